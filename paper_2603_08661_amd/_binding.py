@@ -145,8 +145,24 @@ def _check(code: int, where: str):
         raise IgspError(code, where)
 
 
+# One igsp_view as a numpy record (the same bytes as View).
+_VIEW_RECORD = np.dtype([("width", np.int32), ("height", np.int32), ("in_offset", np.int64), ("out_offset", np.int64)])
+assert _VIEW_RECORD.itemsize == ctypes.sizeof(View)
+# Up to this many views a Python loop is as fast as the array operations
+# (about 1.2 us a view against 8 us for the table and 7 us for its extents).
+_FEW_VIEWS = 8
+
+
 def view_table(widths, heights, in_offset, out_offset):
     n = len(widths)
+    cols = (widths, heights, in_offset, out_offset)
+    if n > _FEW_VIEWS and all(type(c) is np.ndarray and c.ndim == 1 and c.dtype.kind in "iu" and c.size >= n for c in cols):
+        # integer arrays are copied column by column: 300 views take 8 us
+        # instead of 380 (a batch's call was bound by this loop)
+        rec = np.empty(n, _VIEW_RECORD)
+        for name, c in zip(_VIEW_RECORD.names, cols):
+            rec[name] = c[:n]
+        return (View * n).from_buffer(rec), n
     arr = (View * max(n, 1))()
     for v in range(n):
         arr[v] = View(int(widths[v]), int(heights[v]), int(in_offset[v]), int(out_offset[v]))
@@ -160,15 +176,13 @@ def _ptr(t) -> int:
 def _stream(stream) -> int:
     import torch
 
-    if stream is None:
-        stream = torch.cuda.current_stream()
+    if stream is None:  # the current device's current stream, without a Stream object (0.3 us against 2.8)
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
     return int(stream.cuda_stream)
 
 
 def _need(t, dtype, name):
-    import torch
-
-    if t is None:
+    if t is None or (t.dtype is dtype and t.is_cuda and t.is_contiguous()):
         return
     if not t.is_cuda:
         raise ValueError(f"{name} must be a device tensor")
@@ -176,7 +190,6 @@ def _need(t, dtype, name):
         raise ValueError(f"{name} must be {dtype}, got {t.dtype}")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
-    _ = torch
 
 
 PLAIN, BATCHED, BATCHED_STAGED, BATCHED_PERSISTENT, UNFUSED = 0, 1, 2, 3, 4
@@ -241,13 +254,32 @@ def edge_importance(images, views, out_maps, precision="fp32", batched=True, seg
            "edge_importance")
 
 
+def _extents(tab, n):
+    """Image bytes and map floats that the views reach."""
+    if n > _FEW_VIEWS:
+        rec = np.frombuffer(tab, _VIEW_RECORD, n)
+        px = rec["width"].astype(np.float64) * rec["height"]
+        ends = float((3.0 * px + rec["in_offset"]).max()), float((px + rec["out_offset"]).max())
+        if max(ends) < 2.0 ** 52:   # exact in float64; larger ones are refused either way, counted in whole numbers
+            return int(ends[0]), int(ends[1])
+    if n < 1:
+        raise ValueError("no views to bound")
+    in_end = out_end = None
+    for v in range(n):
+        t = tab[v]
+        px = t.width * t.height
+        a, b = t.in_offset + 3 * px, t.out_offset + px
+        in_end = a if in_end is None or a > in_end else in_end
+        out_end = b if out_end is None or b > out_end else out_end
+    return in_end, out_end
+
+
 def _check_extents(tab, n, images, out_maps, medians=None, survivors=None):
     """The C ABI trusts the caller that every view lies inside both buffers;
     check it here, where the tensor sizes are known."""
     if n == 0:
         return
-    in_end = max(tab[v].in_offset + 3 * tab[v].width * tab[v].height for v in range(n))
-    out_end = max(tab[v].out_offset + tab[v].width * tab[v].height for v in range(n))
+    in_end, out_end = _extents(tab, n)
     if in_end > images.numel():
         raise ValueError(f"views need {in_end} image bytes, the tensor has {images.numel()}")
     if out_end > out_maps.numel():
@@ -406,7 +438,7 @@ def split_mask(maps, views, gauss, view, pixel, weight, grad, count, mask, score
         raise ValueError("grad and scores need capacity entries")
     tab, nv = view_table(*views)
     if nv:
-        out_end = max(tab[v].out_offset + tab[v].width * tab[v].height for v in range(nv))
+        out_end = _extents(tab, nv)[1]
         if out_end > maps.numel():
             raise ValueError(f"views need {out_end} map floats, the tensor has {maps.numel()}")
     c = Contributions(_ptr(gauss), _ptr(view), _ptr(pixel), _ptr(weight), n)
