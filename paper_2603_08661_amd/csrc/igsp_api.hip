@@ -665,8 +665,8 @@ igsp_status enqueue_las(LasPlan* P, const igsp_gaussians* g, const igsp_adam_mom
 // Workspace of long_axis_split_noalloc: the per-tile selected counts, their
 // exclusive offsets and the split's scalars, in a fixed device array (one
 // copy per GPU, held until the process ends). Nothing in it needs to start at
-// zero: the count kernel writes every live tile's count, the scan kernel every
-// live tile's offset and all the scalars, before anything reads them.
+// zero: the count kernel writes every live tile's count and N, the scan kernel
+// every live tile's offset and the decision, before anything reads them.
 constexpr int64_t kNoAllocCapacity = int64_t(1) << 28;   // rows
 constexpr int kNoAllocTiles = (int)(kNoAllocCapacity / kLasRows);
 struct LasScratch {

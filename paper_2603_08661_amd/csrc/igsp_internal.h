@@ -195,13 +195,19 @@ int persistent_blocks_per_cu(int precision, int wg_waves);
 constexpr int kLasThreads = 256;
 constexpr int kLasRounds = 8;
 constexpr int kLasRows = kLasThreads * kLasRounds;  // rows per tile (8 per thread)
-constexpr int kLasGrid = 1024;                      // work-groups of the count and split kernels
+constexpr int kLasFoldTiles = 2048;                 // up to this many tiles: one work-group per tile, no scan launch
+constexpr int kLasGrid = 2048;                      // work-groups of the count and split kernels above that
 
 struct LasScalars {
   int64_t n_live;    // N read before the split
-  int64_t k;         // rows selected
   int32_t ok;        // 1 if the split proceeds
   int32_t pad;
+};
+
+// Row-wide work of the full-record split, one job per work-group of a tile.
+enum : int32_t { kJobFeatures = 0, kJobFeatMoment0 = 1, kJobFeatMoment1 = 2, kJobMoments0 = 3, kJobMoments1 = 4 };
+struct LasJobs {
+  int32_t job[5];
 };
 
 struct LasLaunch {

@@ -1,20 +1,23 @@
 // Long-Axis-Split on gfx950 (Sec. 2.2 of arXiv 2603.08661, Algorithm 1 with
 // the column-extraction transform of Algorithm 2).
 //
-// Three launches, so the split is all-or-nothing and the live count N can
-// stay on the device (a captured graph stays valid as N grows); a small plain
-// split (capacity <= 65536 rows) runs the same steps in one work-group and
-// one launch (las_small_kernel):
+// The split is all-or-nothing and the live count N stays on the device (a
+// captured graph stays valid as N grows), so every launch is shaped by the
+// capacity alone:
 //   las_count : per tile of 2048 live rows, the number of selected rows
 //               (8 mask bytes per lane, a byte-wise non-zero test, popcount);
 //   las_scan  : one work-group: exclusive scan of the live tiles' counts, K,
-//               the capacity decision, status, and the new count N + K;
+//               the capacity decision, status, and the new count N + K; only
+//               for capacities above kLasFoldTiles tiles, below that every
+//               split work-group sums the counts itself;
 //   las_split : per tile, the selected rows compacted in ascending order in
 //               LDS, then split with every lane busy: child A in place at row
 //               i, child B appended at row N + rank (consecutive lanes write
-//               consecutive rows), split_idx[rank] = i.
-// Count and split work-groups stride over the live tiles with a grid fixed
-// by the capacity, so a captured graph stays valid as N grows.
+//               consecutive rows), split_idx[rank] = i. The full-record form
+//               gives the feature copy, each feature moment and the narrow
+//               moments of a tile a work-group of their own.
+// A small plain split (capacity <= 65536 rows) runs the same steps in one
+// work-group and one launch (las_small_kernel).
 // All split arithmetic is FP32 in registers; the paper's transform reads
 // only column l of R, computed straight from the normalised quaternion.
 
@@ -82,6 +85,8 @@ __global__ __launch_bounds__(kLasThreads) void las_count_kernel(LasLaunch L) {
   __shared__ int wsum[kLasThreads / 64];
   const int64_t N = live_rows(L);
   const int nt = tiles_of(N);
+  // the split may overwrite the caller's count: its other work-groups read N here
+  if (blockIdx.x == 0 && threadIdx.x == 0) L.scalars->n_live = *L.g.count;
   for (int t = blockIdx.x; t < nt; t += gridDim.x) {
     const int64_t i0 = (int64_t)t * kLasRows + 8 * threadIdx.x;
     const int c = __popcll(nonzero_bytes(mask8(L, i0, N)));
@@ -89,6 +94,17 @@ __global__ __launch_bounds__(kLasThreads) void las_count_kernel(LasLaunch L) {
     (void)wg_scan<kLasThreads>(c, wsum, total);
     if (threadIdx.x == 0) L.block_counts[t] = total;
   }
+}
+
+// The capacity decision of a split of K rows: true if it proceeds.
+__device__ __forceinline__ bool split_fits(const LasLaunch& L, int64_t n_raw, int64_t K) {
+  return n_raw >= 0 && n_raw <= L.g.capacity && n_raw + K <= L.g.capacity;
+}
+
+__device__ __forceinline__ void report_split(const LasLaunch& L, int64_t n_raw, int64_t K, bool ok) {
+  *L.status = ok ? IGSP_OK : IGSP_ERR_CAPACITY;
+  if (L.n_split) *L.n_split = K;
+  if (ok) *L.g.count = n_raw + K;
 }
 
 // One work-group: exclusive scan of the live tiles' counts, K, the capacity
@@ -124,15 +140,22 @@ __global__ __launch_bounds__(1024) void las_scan_kernel(LasLaunch L) {
     }
   if (tid == 0) {
     const int64_t n_raw = *L.g.count;
-    const bool valid = n_raw >= 0 && n_raw <= L.g.capacity;
-    const bool ok = valid && n_raw + K <= L.g.capacity;
-    L.scalars->n_live = n_raw;
-    L.scalars->k = K;
+    const bool ok = split_fits(L, n_raw, K);
     L.scalars->ok = ok ? 1 : 0;
-    *L.status = ok ? IGSP_OK : IGSP_ERR_CAPACITY;
-    if (L.n_split) *L.n_split = K;
-    if (ok) *L.g.count = n_raw + K;
+    report_split(L, n_raw, K, ok);
   }
+}
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// Non-temporal store, for rows scattered over an array larger than the caches:
+// each line is written once and not read again by the split. 600k of 3M
+// 192-byte rows zeroed: 36 us with plain stores, 26 us with these; 16-byte
+// rows 18 and 13 us (arrays in turn, none cached). Contiguous spans and the
+// split's own rows (read just before) are not faster with them.
+template <class T>
+__device__ __forceinline__ void put_nt(T* p, T v) {
+  __builtin_nontemporal_store(v, p);
 }
 
 // The split of selected row i into child A (row i) and child B (row j).
@@ -188,7 +211,7 @@ __device__ __forceinline__ void split_row(const LasLaunch& L, int64_t i, int64_t
 // stores. A parent's moment row of at most 4 floats is cleared by one lane;
 // a wider row (features, their moments) by consecutive lanes, 64 / w rows per
 // wavefront step (the lane's row and element come from divisions done once),
-// each lane moving one float, or one float4 when the row width is a
+// each lane moving one float, or one 16-byte word when the row width is a
 // multiple of 4 and the array 16-byte aligned.
 
 // Zero n floats from p (p 4-byte aligned): 16-byte stores in the aligned middle.
@@ -198,7 +221,7 @@ __device__ __forceinline__ void zero_span(float* p, int64_t n) {
   float* q = p + head;
   const int64_t m = n - head, m4 = m / 4;
   for (int64_t k = threadIdx.x; k < m4; k += kLasThreads)
-    reinterpret_cast<float4*>(q)[k] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    reinterpret_cast<f32x4*>(q)[k] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
   for (int64_t k = 4 * m4 + threadIdx.x; k < m; k += kLasThreads) q[k] = 0.0f;
 }
 
@@ -232,10 +255,10 @@ __device__ __forceinline__ void zero_parents(float* a, int w, const RowLanes& rl
   constexpr int NWV = kLasThreads / 64;
   if (rl.rpw > 0) {
     if (rl.lr < 0) return;
-    for (int r = wv * rl.rpw + rl.lr; r < total; r += NWV * rl.rpw) a[(base + rows[r]) * w + rl.le] = 0.0f;
+    for (int r = wv * rl.rpw + rl.lr; r < total; r += NWV * rl.rpw) put_nt(a + (base + rows[r]) * w + rl.le, 0.0f);
   } else {
     for (int r = wv; r < total; r += NWV)
-      for (int e = rl.le; e < w; e += 64) a[(base + rows[r]) * w + e] = 0.0f;
+      for (int e = rl.le; e < w; e += 64) put_nt(a + (base + rows[r]) * w + e, 0.0f);
   }
 }
 
@@ -248,8 +271,8 @@ constexpr int kWideInFlight = 4;
 __device__ __forceinline__ bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
 // dst row N + first + r = src row base + rows[r] for the tile's r < total
-// (w4 = row width in float4).
-__device__ __forceinline__ void copy_rows4(float4* a, int w4, const int32_t* rows, int64_t base, int64_t dst0,
+// (w4 = row width in 16-byte words).
+__device__ __forceinline__ void copy_rows4(f32x4* a, int w4, const int32_t* rows, int64_t base, int64_t dst0,
                                            int total) {
   const RowLanes rl = row_lanes(w4);
   const int wv = threadIdx.x >> 6;
@@ -264,12 +287,12 @@ __device__ __forceinline__ void copy_rows4(float4* a, int w4, const int32_t* row
       static_assert(kWideInFlight == 4, "four named rows in flight");
       const int ra = min(r0, total - 1), rb = min(r0 + step, total - 1), rc = min(r0 + 2 * step, total - 1),
                 rd = min(r0 + 3 * step, total - 1);
-      const float4 va = a[(base + rows[ra]) * w4 + rl.le], vb = a[(base + rows[rb]) * w4 + rl.le],
-                   vc = a[(base + rows[rc]) * w4 + rl.le], vd = a[(base + rows[rd]) * w4 + rl.le];
-      a[(dst0 + ra) * w4 + rl.le] = va;
-      a[(dst0 + rb) * w4 + rl.le] = vb;
-      a[(dst0 + rc) * w4 + rl.le] = vc;
-      a[(dst0 + rd) * w4 + rl.le] = vd;
+      const f32x4 va = a[(base + rows[ra]) * w4 + rl.le], vb = a[(base + rows[rb]) * w4 + rl.le],
+                  vc = a[(base + rows[rc]) * w4 + rl.le], vd = a[(base + rows[rd]) * w4 + rl.le];
+      put_nt(a + (dst0 + ra) * w4 + rl.le, va);
+      put_nt(a + (dst0 + rb) * w4 + rl.le, vb);
+      put_nt(a + (dst0 + rc) * w4 + rl.le, vc);
+      put_nt(a + (dst0 + rd) * w4 + rl.le, vd);
     }
   } else {
     for (int r = wv; r < total; r += NWV)
@@ -278,17 +301,17 @@ __device__ __forceinline__ void copy_rows4(float4* a, int w4, const int32_t* row
 }
 
 // The tile's parent rows of a wide array cleared with 16-byte stores.
-__device__ __forceinline__ void zero_parents4(float4* a, int w4, const int32_t* rows, int64_t base, int total) {
+__device__ __forceinline__ void zero_parents4(f32x4* a, int w4, const int32_t* rows, int64_t base, int total) {
   const RowLanes rl = row_lanes(w4);
   const int wv = threadIdx.x >> 6;
   constexpr int NWV = kLasThreads / 64;
-  const float4 z = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+  const f32x4 z = {0.0f, 0.0f, 0.0f, 0.0f};
   if (rl.rpw > 0) {
     if (rl.lr < 0) return;
-    for (int r = wv * rl.rpw + rl.lr; r < total; r += NWV * rl.rpw) a[(base + rows[r]) * w4 + rl.le] = z;
+    for (int r = wv * rl.rpw + rl.lr; r < total; r += NWV * rl.rpw) put_nt(a + (base + rows[r]) * w4 + rl.le, z);
   } else {
     for (int r = wv; r < total; r += NWV)
-      for (int e = rl.le; e < w4; e += 64) a[(base + rows[r]) * w4 + e] = z;
+      for (int e = rl.le; e < w4; e += 64) put_nt(a + (base + rows[r]) * w4 + e, z);
   }
 }
 
@@ -298,20 +321,22 @@ __device__ __forceinline__ void zero_parents_rows(float* a, const int32_t* rows,
   for (int r = threadIdx.x; r < total; r += kLasThreads) {
     float* p = a + (base + rows[r]) * W;
 #pragma unroll
-    for (int j = 0; j < W; ++j) p[j] = 0.0f;
+    for (int j = 0; j < W; ++j) put_nt(p + j, 0.0f);
   }
 }
 
-__device__ __forceinline__ void row_work(const LasLaunch& L, const int32_t* rows, int64_t base, int64_t N,
-                                         int64_t first, int total) {
+// One array group's share of a tile's row-wide work.
+__device__ __forceinline__ void row_job(const LasLaunch& L, int job, const int32_t* rows, int64_t base, int64_t N,
+                                        int64_t first, int total) {
   const int F = L.g.feat_dim;
   const int wv = threadIdx.x >> 6;
   constexpr int NWV = kLasThreads / 64;
   const bool wideF = F > 0 && (F & 3) == 0;
-  if (F > 0) {  // second children's features from the parents
+  const igsp_adam_moments& A = L.adam;
+  if (job == kJobFeatures) {  // second children's features from the parents
     float* f = L.g.features;
     if (wideF && aligned16(f)) {
-      copy_rows4(reinterpret_cast<float4*>(f), F / 4, rows, base, N + first, total);
+      copy_rows4(reinterpret_cast<f32x4*>(f), F / 4, rows, base, N + first, total);
     } else {
       const RowLanes rl = row_lanes(F);
       if (rl.rpw > 0) {
@@ -323,10 +348,13 @@ __device__ __forceinline__ void row_work(const LasLaunch& L, const int32_t* rows
           for (int e = rl.le; e < F; e += 64) f[(N + first + r) * F + e] = f[(base + rows[r]) * F + e];
       }
     }
-  }
-  const igsp_adam_moments& A = L.adam;
-#pragma unroll
-  for (int m = 0; m < 2; ++m) {
+  } else if (job == kJobFeatMoment0 || job == kJobFeatMoment1) {
+    float* const fm = A.features[job - kJobFeatMoment0];
+    if (wideF && aligned16(fm)) zero_parents4(reinterpret_cast<f32x4*>(fm), F / 4, rows, base, total);
+    else zero_parents(fm, F, row_lanes(F), rows, base, total);
+    zero_span(fm + (N + first) * F, (int64_t)total * F);
+  } else {
+    const int m = job - kJobMoments0;
     float* const narrow[4] = {A.means[m], A.log_scales[m], A.quats[m], A.opacity_logits[m]};
     const int width[4] = {3, 3, 4, 1};
     if (narrow[0]) zero_parents_rows<3>(narrow[0], rows, base, total);
@@ -336,29 +364,74 @@ __device__ __forceinline__ void row_work(const LasLaunch& L, const int32_t* rows
 #pragma unroll
     for (int k = 0; k < 4; ++k)
       if (narrow[k]) zero_span(narrow[k] + (N + first) * width[k], (int64_t)total * width[k]);
-    float* const fm = F > 0 ? A.features[m] : nullptr;
-    if (fm) {
-      if (wideF && aligned16(fm)) zero_parents4(reinterpret_cast<float4*>(fm), F / 4, rows, base, total);
-      else zero_parents(fm, F, row_lanes(F), rows, base, total);
-      zero_span(fm + (N + first) * F, (int64_t)total * F);
-    }
+  }
+}
+
+// Selected rows of the tiles before tile t (of nt) and of all tiles, by one
+// work-group of NT threads from the per-tile counts.
+template <int NT>
+__device__ __forceinline__ void sum_counts(const int32_t* counts, int nt, int t, int* wsum /* [2 * NT / 64] */,
+                                           int& before, int& all) {
+  int b = 0, a = 0;
+#pragma unroll 8
+  for (int k = threadIdx.x; k < nt; k += NT) {
+    const int c = counts[k];
+    a += c;
+    b += k < t ? c : 0;
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    a += __shfl_xor(a, o, 64);
+    b += __shfl_xor(b, o, 64);
+  }
+  const int w = threadIdx.x >> 6;
+  if ((threadIdx.x & 63) == 0) {
+    wsum[2 * w] = a;
+    wsum[2 * w + 1] = b;
+  }
+  __syncthreads();
+  all = before = 0;
+#pragma unroll
+  for (int k = 0; k < NT / 64; ++k) {
+    all += wsum[2 * k];
+    before += wsum[2 * k + 1];
   }
 }
 
 // Per live tile: the selected rows, compacted in ascending order into LDS
 // (each thread owns 8 consecutive rows; a work-group scan places them), then
 // split with every lane busy: consecutive lanes take consecutive ranks, so
-// the appended children of a wavefront are contiguous rows. FULL adds the
-// row-wide work (feature rows, optimiser moments); the plain split (no
-// features, no moments) is compiled without it, so it keeps its registers
-// for the split itself.
-template <bool FULL>
-__device__ __forceinline__ void split_tiles(const LasLaunch& L) {
+// the appended children of a wavefront are contiguous rows. FULL runs the
+// tile's row-wide work (feature rows, optimiser moments) beside the split, one
+// job per blockIdx.y, each a work-group that compacts the tile's rows again
+// (2 KiB of mask). Bound by the memory lines touched (1.11 GB for 3M rows,
+// 600k selected, F = 48, all moments): 393 us with one work-group per tile
+// doing every job in turn, 381 us with jobs of their own, 310 us with
+// non-temporal stores to the scattered rows and the copied children. The jobs
+// run array by array; a tile's jobs side by side took 334 us.
+// FOLD: the launch has one work-group (per job) for every tile of the
+// capacity, and each sums the tile counts itself (8 KiB from L2 at most):
+// 1M rows 22.4 -> 17.5 us a call without the scan launch, 3M rows unchanged.
+// Above kLasFoldTiles the sums would grow with the square of the tiles.
+template <bool FULL, bool FOLD>
+__device__ __forceinline__ void split_tiles(const LasLaunch& L, const LasJobs& J) {
   __shared__ int32_t rows[kLasRows];
-  __shared__ int wsum[kLasThreads / 64];
-  if (!L.scalars->ok) return;  // uniform across the grid
-  const int64_t N = L.scalars->n_live;
+  __shared__ int wsum[2 * kLasThreads / 64];
+  const int64_t n_raw = L.scalars->n_live;
+  const int64_t N = n_raw < 0 ? 0 : (n_raw > L.g.capacity ? L.g.capacity : n_raw);
   const int nt = tiles_of(N);
+  int64_t first = 0;
+  if constexpr (FOLD) {
+    int before = 0, all = 0;
+    sum_counts<kLasThreads>(L.block_counts, nt, blockIdx.x, wsum, before, all);
+    const bool ok = split_fits(L, n_raw, all);
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) report_split(L, n_raw, all, ok);
+    if (!ok) return;  // uniform across the grid
+    first = before;
+    __syncthreads();  // wsum is used again
+  } else {
+    if (!L.scalars->ok) return;  // uniform across the grid
+  }
   for (int t = blockIdx.x; t < nt; t += gridDim.x) {
     const int64_t base = (int64_t)t * kLasRows;
     const uint64_t nz = nonzero_bytes(mask8(L, base + 8 * threadIdx.x, N));
@@ -368,23 +441,29 @@ __device__ __forceinline__ void split_tiles(const LasLaunch& L) {
     for (int k = 0; k < 8; ++k)
       if ((nz >> (8 * k)) & 1ull) rows[pos++] = 8 * threadIdx.x + k;
     __syncthreads();
-    const int64_t first = L.block_offsets[t];
-    for (int k = threadIdx.x; k < total; k += kLasThreads) {
-      const int64_t rank = first + k;
-      split_row(L, base + rows[k], N + rank, rank);
+    if constexpr (!FOLD) first = L.block_offsets[t];
+    if (!FULL || blockIdx.y == 0) {
+      for (int k = threadIdx.x; k < total; k += kLasThreads) {
+        const int64_t rank = first + k;
+        split_row(L, base + rows[k], N + rank, rank);
+      }
+    } else {
+      row_job(L, J.job[blockIdx.y - 1], rows, base, N, first, total);
     }
-    if constexpr (FULL) row_work(L, rows, base, N, first, total);
     __syncthreads();  // rows[] is rewritten by the next tile
   }
 }
 
 // The plain split fits 64 registers: eight waves per SIMD.
+template <bool FOLD>
 __global__ __launch_bounds__(kLasThreads) __attribute__((amdgpu_waves_per_eu(8))) void las_split_kernel(LasLaunch L) {
-  split_tiles<false>(L);
+  split_tiles<false, FOLD>(L, LasJobs{});
 }
 
-__global__ __launch_bounds__(kLasThreads) __attribute__((amdgpu_waves_per_eu(4))) void las_split_full_kernel(LasLaunch L) {
-  split_tiles<true>(L);
+template <bool FOLD>
+__global__ __launch_bounds__(kLasThreads) __attribute__((amdgpu_waves_per_eu(4))) void las_split_full_kernel(LasLaunch L,
+                                                                                                          LasJobs J) {
+  split_tiles<true, FOLD>(L, J);
 }
 
 // A small plain split (capacity <= kLasSmallCapacity rows) in one launch by
@@ -411,14 +490,8 @@ __global__ __launch_bounds__(kSmallThreads) void las_small_kernel(LasLaunch L) {
   }
   if (threadIdx.x == 0) {
     const int64_t n_raw = *L.g.count;
-    const bool valid = n_raw >= 0 && n_raw <= L.g.capacity;
-    const bool ok = valid && n_raw + K <= L.g.capacity;
-    L.scalars->n_live = n_raw;
-    L.scalars->k = K;
-    L.scalars->ok = ok ? 1 : 0;
-    *L.status = ok ? IGSP_OK : IGSP_ERR_CAPACITY;
-    if (L.n_split) *L.n_split = K;
-    if (ok) *L.g.count = n_raw + K;
+    const bool ok = split_fits(L, n_raw, K);
+    report_split(L, n_raw, K, ok);
     s_ok = ok ? 1 : 0;
   }
   __syncthreads();
@@ -443,24 +516,35 @@ __global__ __launch_bounds__(kSmallThreads) void las_small_kernel(LasLaunch L) {
 
 hipError_t launch_las(const LasLaunch& L, hipStream_t s) {
   const igsp_adam_moments& A = L.adam;
-  bool full = L.g.feat_dim > 0;
-  for (int m = 0; m < 2; ++m)
-    full = full || A.means[m] || A.log_scales[m] || A.quats[m] || A.opacity_logits[m] || A.features[m];
-  if (!full && L.g.capacity <= kLasSmallCapacity) {
+  LasJobs J{};
+  int jobs = 0;
+  if (L.g.feat_dim > 0) J.job[jobs++] = kJobFeatures;
+  for (int m = 0; m < 2; ++m) {
+    if (A.features[m]) J.job[jobs++] = kJobFeatMoment0 + m;
+    if (A.means[m] || A.log_scales[m] || A.quats[m] || A.opacity_logits[m]) J.job[jobs++] = kJobMoments0 + m;
+  }
+  const dim3 block(kLasThreads);
+  if (jobs == 0 && L.g.capacity <= kLasSmallCapacity) {
     hipLaunchKernelGGL(las_small_kernel, dim3(1), dim3(kSmallThreads), 0, s, L);
     return hipGetLastError();
   }
   // grids are fixed by the capacity (the live count is only known on the
-  // device); work-groups stride over the live tiles
-  const int grid = L.n_blocks < kLasGrid ? L.n_blocks : kLasGrid;
-  hipLaunchKernelGGL(las_count_kernel, dim3(grid), dim3(kLasThreads), 0, s, L);
+  // device): one work-group per tile, or work-groups striding over the live tiles
+  const bool fold = L.n_blocks <= kLasFoldTiles;
+  const int grid = fold || L.n_blocks < kLasGrid ? L.n_blocks : kLasGrid;
+  hipLaunchKernelGGL(las_count_kernel, dim3(grid), block, 0, s, L);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(las_scan_kernel, dim3(1), dim3(1024), 0, s, L);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  if (full) hipLaunchKernelGGL(las_split_full_kernel, dim3(grid), dim3(kLasThreads), 0, s, L);
-  else hipLaunchKernelGGL(las_split_kernel, dim3(grid), dim3(kLasThreads), 0, s, L);
+  if (!fold) {
+    hipLaunchKernelGGL(las_scan_kernel, dim3(1), dim3(1024), 0, s, L);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  const dim3 g(grid, 1 + jobs);
+  if (jobs && fold) hipLaunchKernelGGL(las_split_full_kernel<true>, g, block, 0, s, L, J);
+  else if (jobs) hipLaunchKernelGGL(las_split_full_kernel<false>, g, block, 0, s, L, J);
+  else if (fold) hipLaunchKernelGGL(las_split_kernel<true>, g, block, 0, s, L);
+  else hipLaunchKernelGGL(las_split_kernel<false>, g, block, 0, s, L);
   return hipGetLastError();
 }
 

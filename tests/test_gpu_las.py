@@ -285,3 +285,23 @@ def test_full_record_split_capacity_overflow_touches_nothing():
         for k in range(2):
             assert (after[grp][k] == before[grp][k]).all()
     assert (res["features"] == res["host"]["features"]).all()
+
+
+@pytest.mark.parametrize("tiles,record", [(2048, False), (2049, False), (2048, True), (2049, True)])
+def test_capacity_on_either_side_of_the_folded_scan(tiles, record):
+    """Up to 2048 tiles of 2048 rows every split work-group sums the tile
+    counts; above that a scan launch does, and work-groups stride over the
+    tiles. Rows are selected in the first, a middle and the last live tile."""
+    N, cap = tiles * 2048 - 5000, tiles * 2048
+    g = synth.gaussians(31, N)
+    mk = np.zeros(N, np.uint8)
+    mk[np.r_[0:700, N // 2:N // 2 + 1500, N - 2300:N]] = 1
+    if record:
+        res, before, after = _run_full(g, N, mk, cap, 4, 33, ("opacity_logits", "features"))
+        ref = compare(res, N, cap, feats=res["host"]["features"])
+        for grp in before:
+            for k in range(2):
+                want = oracle.las_moments(N, ref["split_idx"], {"x": before[grp][k]})["x"]
+                assert (after[grp][k] == want).all(), (grp, k)
+    else:
+        compare(run_las(g, N, mk, cap), N, cap)
