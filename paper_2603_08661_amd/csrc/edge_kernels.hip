@@ -15,7 +15,8 @@
 //     register sliding windows; horizontal neighbours cross lanes with DPP
 //     wave shifts, never through LDS.
 //   - Each lane reads its 12 bytes of a row with one unaligned 96-bit buffer
-//     load, one row ahead of its use; a wave's loads cover 768 contiguous
+//     load, five rows ahead of its use (one row ahead: 1.2% slower, 150 views
+//     of 2473x1643 and half, 0.904 against 0.893 ms of edge maps); a wave's loads cover 768 contiguous
 //     bytes. Row indices, descriptors and bounds are wave-uniform scalar
 //     work, and the loop body issues the same memory operations on every
 //     lane (a wavefront's store of one row fills one 256-value slot of its
@@ -68,6 +69,15 @@ __device__ __forceinline__ gptr<T> as_global(T* p) {
 template <class T>
 __device__ __forceinline__ gptr<const T> as_global(const T* p) {
   return (gptr<const T>)p;
+}
+
+// Memory that no work-group of the launch writes, read through the scalar
+// cache where the address is uniform.
+template <class T>
+using cptr = const __attribute__((address_space(4))) T*;
+template <class T>
+__device__ __forceinline__ cptr<T> as_constant(const T* p) {
+  return (cptr<T>)p;
 }
 
 // ------------------------------------------------------------- cross-lane
@@ -269,8 +279,9 @@ __device__ __forceinline__ bool keep_of(const Dir& d, float m, float Ul, float U
 // windows are kept twice and addressed by the parity of the row, the
 // magnitude rows three times and addressed by the row modulo 3, so after
 // unrolling the loop by six every value stays in its register (no copies).
+template <int D>
 struct StripState {
-  Lane12 rows[2];                  // raw bytes: this row / next row
+  Lane12 rows[D];                  // raw bytes: this row and the next D - 1
   // rows r-1 (other parity slot) and r-2 (same parity slot) of:
   int h[2][4];                     // the horizontal blur
   int e[2][4];                     // e(r) = h(r) + h(r-2)
@@ -312,24 +323,32 @@ __device__ __forceinline__ Lane12 fetch_row(const StripCtx& C, int yy) {
   else return load_lane(row, C.win_off);
 }
 
-template <int PREC, bool NARROW, int P, int MS, int CPOL>
-__device__ __forceinline__ void strip_row(const StripCtx& C, StripState& S, int t, uint32_t* hist) {
+// Rows of raw bytes held (a divisor of 6). The byte-by-byte loads of a narrow
+// view's row take twelve registers until they are put together.
+template <bool NARROW>
+constexpr int kRowsHeld = NARROW ? 2 : 6;
+
+// K = t mod 6.
+template <int PREC, bool NARROW, int K, int CPOL>
+__device__ __forceinline__ void strip_row(const StripCtx& C, StripState<kRowsHeld<NARROW>>& S, int t, uint32_t* hist) {
+  constexpr int D = kRowsHeld<NARROW>;
   using St = Store<PREC>;
+  constexpr int P = K % 2, MS = K % 3;
   constexpr int Q = P ^ 1;             // previous row's parity slot
   constexpr int MD = MS;               // magnitude slots: new (down) row,
   constexpr int MC = (MS + 2) % 3;     // the row before it (centre),
   constexpr int MU = (MS + 1) % 3;     // and the one before that (up)
   constexpr int ES = sizeof(typename St::T);
-  // ---- prefetch the next row (the last step re-reads a row: one load per
-  //      step keeps the wait for this row from draining the prefetch)
-  S.rows[Q] = fetch_row<NARROW>(C, min(C.ys - kHalo + t + 1, C.ye + kHalo - 1));
+  // ---- prefetch the row D - 1 rows ahead (the last steps re-read a row: one
+  //      load per step keeps the wait for this row from draining the prefetch)
+  S.rows[(K + D - 1) % D] = fetch_row<NARROW>(C, min(C.ys - kHalo + t + D - 1, C.ye + kHalo - 1));
 
   // ---- 1. grayscale of row yy = ys - 4 + t (edge strips first put the
   //      mirrored pixels of the window in lane order: two byte permutes per
   //      output word, the first over window bytes 0-7, the second adding
   //      bytes 8-11)
   int g[4];
-  uint32_t d0 = S.rows[P].v.x, d1 = S.rows[P].v.y, d2 = S.rows[P].v.z;
+  uint32_t d0 = S.rows[K % D].v.x, d1 = S.rows[K % D].v.y, d2 = S.rows[K % D].v.z;
   if (!NARROW && C.remap) {
     asm volatile("");  // keeps this a branch that interior strips skip, not selects every strip pays for
     const uint32_t o0 = __builtin_amdgcn_perm(d2, __builtin_amdgcn_perm(d1, d0, C.permA[0]), C.permB[0]);
@@ -458,18 +477,19 @@ __device__ __forceinline__ void strip_row(const StripCtx& C, StripState& S, int 
 
 template <int PREC, bool NARROW, int CPOL>
 __device__ __forceinline__ void march(const StripCtx& C, uint32_t* hist) {
-  StripState S = {};
-  S.rows[0] = fetch_row<NARROW>(C, C.ys - kHalo);
+  StripState<kRowsHeld<NARROW>> S = {};
+#pragma unroll
+  for (int k = 0; k < kRowsHeld<NARROW> - 1; ++k) S.rows[k] = fetch_row<NARROW>(C, min(C.ys - kHalo + k, C.ye + kHalo - 1));
   // six rows per iteration (parity slot t % 2, magnitude slot t % 3), with no
   // exit inside the body: rows past the strip's last one (up to five) are
   // computed and neither stored nor counted
   for (int t = 0; t < C.T; t += 6) {
-    strip_row<PREC, NARROW, 0, 0, CPOL>(C, S, t, hist);
-    strip_row<PREC, NARROW, 1, 1, CPOL>(C, S, t + 1, hist);
-    strip_row<PREC, NARROW, 0, 2, CPOL>(C, S, t + 2, hist);
-    strip_row<PREC, NARROW, 1, 0, CPOL>(C, S, t + 3, hist);
-    strip_row<PREC, NARROW, 0, 1, CPOL>(C, S, t + 4, hist);
-    strip_row<PREC, NARROW, 1, 2, CPOL>(C, S, t + 5, hist);
+    strip_row<PREC, NARROW, 0, CPOL>(C, S, t, hist);
+    strip_row<PREC, NARROW, 1, CPOL>(C, S, t + 1, hist);
+    strip_row<PREC, NARROW, 2, CPOL>(C, S, t + 2, hist);
+    strip_row<PREC, NARROW, 3, CPOL>(C, S, t + 3, hist);
+    strip_row<PREC, NARROW, 4, CPOL>(C, S, t + 4, hist);
+    strip_row<PREC, NARROW, 5, CPOL>(C, S, t + 5, hist);
   }
 }
 
@@ -546,11 +566,18 @@ __device__ __forceinline__ void wave_strip(const EdgeLaunch& L, const ViewDesc& 
 template <int PREC, int NW>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(IGSP_FUSED_WAVES_PER_EU))) void edge_fused_kernel(EdgeLaunch L, int item0, int n_items) {
   constexpr int NB = Keys<PREC>::bins;
-  __shared__ uint32_t hist[NB];
+  static_assert(NB % 4 == 0, "whole 16-byte words");
+  __shared__ __attribute__((aligned(16))) uint32_t hist[NB];
   const int item = item0 + xcd_remap((int)blockIdx.x, n_items);
   const EdgeItem it = L.items[item];
   const ViewDesc vd = L.views[it.view];
-  for (int i = threadIdx.x; i < NB; i += NW * 64) hist[i] = 0;
+  for (int i = threadIdx.x; i < NB / 4; i += NW * 64) reinterpret_cast<u32x4*>(hist)[i] = u32x4{0u, 0u, 0u, 0u};
+  // the short chain's counts start from zero (the long chain's selection
+  // launch clears them itself)
+  if (L.short_chain && it.x0 == 0 && it.y0 == 0) {
+    if (threadIdx.x < 8) L.rhist[(int64_t)it.view * kRefineBins + threadIdx.x] = 0;
+    if (L.cand_n && threadIdx.x == 0) L.cand_n[it.view] = 0;
+  }
   __syncthreads();
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int ys = it.y0 + w * L.seg_rows;
@@ -558,9 +585,17 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(IGSP_FU
   if (ys < ye) wave_strip<PREC>(L, vd, it.x0, ys, ye, hist);
   __syncthreads();
   gptr<uint32_t> gh = as_global(L.hist) + (int64_t)it.view * kBinsMax;
-  for (int i = threadIdx.x; i < NB; i += NW * 64) {
-    const uint32_t c = hist[i];
-    if (c) atomicAdd((uint32_t*)(gh + i), c);
+  // (four bins' reads in flight per thread; consecutive lanes add to
+  // consecutive bins: one 16-byte word of bins per lane spreads each atomic
+  // over four times the lines, 17.8 -> 22.6 us for a 1297x840 view)
+  constexpr int NT = NW * 64;
+  for (int i = threadIdx.x; i < NB; i += 4 * NT) {
+    uint32_t c[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) c[k] = hist[min(i + k * NT, NB - 1)];
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if (i + k * NT < NB && c[k]) atomicAdd((uint32_t*)(gh + i + k * NT), c[k]);
   }
 }
 
@@ -575,13 +610,6 @@ __host__ __device__ constexpr int refine_passes(int prec) {
   return prec == IGSP_BF16 ? 0 : (prec == IGSP_FP16 ? 1 : 2);
 }
 __host__ __device__ constexpr int refine_digit_bits(int prec) { return prec == IGSP_FP16 ? 3 : 8; }
-// Whether the normalisation takes the last selection step itself (every
-// work-group from the last pass's histogram) instead of a launch of its own
-// before it. Measured on the same box: FP32 (300 views) 2.78 -> 2.67-2.68 ms
-// for the edge maps; FP16 (200 views) 0.69 -> 0.72-0.73 ms, so FP16 keeps
-// the separate step.
-__host__ __device__ constexpr bool fold_last_step(int prec) { return prec == IGSP_FP32; }
-
 __device__ __forceinline__ void finish_view(const EdgeLaunch& L, int v, MedState& st, bool outputs = true) {
   st.med = st.n ? __uint_as_float(st.prefix << st.shift) : 0.0f;
   if (!outputs) return;
@@ -593,19 +621,28 @@ __device__ __forceinline__ void finish_view(const EdgeLaunch& L, int v, MedState
   if (L.survivors) L.survivors[v] = (int32_t)st.n;
 }
 
+// Inclusive scan over a wavefront's lanes with DPP row shifts and broadcasts
+// (a shuffle per step waits for the LDS pipe six times over).
+__device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) {
+  int x = (int)v;
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);  // row_shr:1
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);  // row_shr:2
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);  // row_shr:4
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);  // row_shr:8
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);  // row_bcast:15 into rows 1 and 3
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);  // row_bcast:31 into rows 2 and 3
+  return (uint32_t)x;
+}
+
 // Block-wide exclusive scan of one value per thread (256 threads).
 __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t* tmp, uint32_t& total) {
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  uint32_t x = v;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const uint32_t y = __shfl_up(x, o, 64);
-    if (lane >= o) x += y;
-  }
+  const uint32_t x = wave_incl_scan(v);
   if (lane == 63) tmp[w] = x;
   __syncthreads();
   uint32_t before = 0;
-  for (int k = 0; k < w; ++k) before += tmp[k];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) before += k < w ? tmp[k] : 0;
   total = tmp[0] + tmp[1] + tmp[2] + tmp[3];
   __syncthreads();
   return before + x - v;
@@ -868,19 +905,207 @@ __global__ __launch_bounds__(256) void median_refine_kernel(EdgeLaunch L, int ch
   if (c) atomicAdd(&L.rhist[(pass * n + v) * kRefineBins + threadIdx.x], c);
 }
 
-// The last selection step of views [v0, v0 + gridDim.x) as a launch of its
-// own (one work-group per view), where the normalisation does not take it.
-__global__ __launch_bounds__(256) void median_step_kernel(EdgeLaunch L, int v0, int pass) {
+// The state a previous launch left, through the scalar cache.
+__device__ __forceinline__ MedState load_uniform(const MedState* s) {
+  cptr<uint32_t> p = as_constant(reinterpret_cast<const uint32_t*>(s));
+  return MedState{p[0], (int32_t)p[1], p[2], p[3], __uint_as_float(p[4]), {0u, 0u, 0u}};
+}
+
+// FP16's only refinement step from its 8 digit counts: few enough that every
+// thread takes it alike, with no barrier.
+__device__ __forceinline__ MedState refine_step8(const MedState& st, cptr<uint32_t> h) {
+  MedState r = st;
+  if (st.n == 0) return r;
+  uint32_t before = 0;
+  int digit = 7;
+  bool found = false;
+#pragma unroll
+  for (int d = 0; d < 8; ++d) {
+    const uint32_t c = h[d];
+    if (!found && before + c > st.rank) {
+      digit = d;
+      found = true;
+    }
+    if (!found) before += c;
+  }
+  r.prefix = (st.prefix << 3) | (uint32_t)digit;
+  r.shift = st.shift - 3;
+  r.rank = st.rank - before;
+  r.med = __uint_as_float(r.prefix << r.shift);
+  return r;
+}
+
+// ---- the short chain (FP32 and FP16, launches of few chunks): every launch
+// costs its start, its end and one memory latency after another, whatever
+// its size, so the median takes one launch between the stencil and the
+// normalisation instead of three. median_gather selects the median's bucket
+// from the first histogram in every work-group (29 KB from L2) and counts
+// (FP16) or lists (FP32) the survivors inside it; the normalisation's
+// work-groups finish the selection from those, and its first chunk of a view
+// clears the histogram. A 256x192 FP32 view's edge maps: 35.9 us with five
+// launches, 25.0 with these three (22.0 with its segments split as well);
+// 1297x840: 40.7 and 32.0. Latency-bound: the stencil's lone wavefronts take
+// 13.5-18 us, the other two launches 5-8 us each.
+
+// The state after the first histogram, taken by a whole work-group (bins: its
+// LDS copy; each thread sums PER consecutive bins, an odd number, so the reads
+// spread over the banks).
+template <int PREC>
+__device__ __forceinline__ MedState select_first(const EdgeLaunch& L, int v, uint32_t* bins, uint32_t* tmp,
+                                                 MedState* s_st) {
+  constexpr int NB = Keys<PREC>::bins, PER = NB / 256;
+  static_assert(NB % 256 == 0 && PER % 2 == 1, "bins per thread");
+  const u32x4* h = reinterpret_cast<const u32x4*>(L.hist + (int64_t)v * kBinsMax);
+#pragma unroll
+  for (int j = 0; j < (NB / 4 + 255) / 256; ++j) {
+    const int i = j * 256 + threadIdx.x;
+    if (i < NB / 4) reinterpret_cast<u32x4*>(bins)[i] = *as_global(h + i);
+  }
+  __syncthreads();
+  uint32_t c[PER], sum = 0;
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    c[k] = bins[threadIdx.x * PER + k];
+    sum += c[k];
+  }
+  uint32_t n = 0;
+  const uint32_t excl = block_excl_scan(sum, tmp, n);
+  const uint32_t k = n ? (n - 1) / 2 : 0;
+  if (n == 0) {
+    if (threadIdx.x == 0) *s_st = MedState{0u, 0, 0u, 0u, 0.0f, {0u, 0u, 0u}};
+  } else if (excl <= k && k < excl + sum) {
+    uint32_t cum = excl;
+    int b = 0;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      if (cum + c[j] > k) { b = j; break; }
+      cum += c[j];
+    }
+    *s_st = MedState{Keys<PREC>::lo + (uint32_t)(threadIdx.x * PER + b), 16, k - cum, n, 0.0f, {0u, 0u, 0u}};
+  }
+  __syncthreads();
+  return *s_st;
+}
+
+// An entry of a view's candidate list: a stored value and how often it occurs.
+__device__ __forceinline__ void add_candidate(const EdgeLaunch& L, const ViewDesc& vd, int v, uint32_t at, uint32_t bits,
+                                              uint32_t n) {
+  if (at < (uint32_t)vd.cand_cap) reinterpret_cast<uint2*>(L.cand)[vd.cand_off + at] = make_uint2(bits, n);
+}
+
+// LDS of median_gather, in words: the first histogram, then (once it has been
+// used) the chunk's candidates and a table of distinct values.
+constexpr int kGatherList = kChunkSlots * kStripCols;  // a chunk's pixels
+constexpr int kGatherTable = 1024;                     // values, then their counts
+static_assert(kGatherList + 2 * kGatherTable <= kBinsMax, "fits the histogram's LDS");
+// A work-group with more candidates than this lists distinct values with
+// their counts (flat graphics put most survivors on a few magnitudes).
+constexpr uint32_t kGatherPlain = 256;
+
+template <int PREC>
+__global__ __launch_bounds__(256) void median_gather_kernel(EdgeLaunch L, int chunk0) {
+  __shared__ __attribute__((aligned(16))) uint32_t lds[kBinsMax];
   __shared__ uint32_t tmp[4];
   __shared__ MedState s_st;
-  const int v = v0 + blockIdx.x;
-  const int64_t n = L.n_views;
-  MedState st = refine_step(L, L.state[(pass - 1) * n + v], L.rhist + ((pass - 1) * n + v) * kRefineBins,
-                            refine_digit_bits(L.precision), tmp, &s_st);
-  if (threadIdx.x == 0) {
-    if (st.shift == final_shift(L.precision)) finish_view(L, v, st);
-    L.state[pass * n + v] = st;
+  __shared__ uint32_t cn, cbase;
+  const RowChunk ck = L.chunks[chunk0 + blockIdx.x];
+  const int v = ck.view;
+  const ViewDesc vd = L.views[v];
+  const int ns = strips_of(vd);
+  const int lane = __lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // a wavefront's share of the chunk (slots past its end: the last one again,
+  // not counted), on its way while the bucket is selected
+  static_assert(kChunkSlots == 4 * kWalkUnroll, "one walk step per wavefront");
+  SlotAt a[kWalkUnroll];
+  float q[kWalkUnroll][4];
+#pragma unroll
+  for (int k = 0; k < kWalkUnroll; ++k) {
+    a[k] = view_slot(vd, ns, min(ck.u0 + wave + 4 * k, ck.u1 - 1), lane);
+    load4<PREC, false>(L, a[k].stored, q[k]);
   }
+  const MedState st = select_first<PREC>(L, v, lds, tmp, &s_st);
+  if (threadIdx.x == 0) {
+    if (L.status && blockIdx.x == 0) *L.status = IGSP_OK;  // the stages cannot fail
+    if (ck.u0 == 0) L.state[v] = st;
+  }
+  if (st.n == 0) return;  // uniform: no survivor
+  if (threadIdx.x < 8) lds[threadIdx.x] = 0;
+  if (threadIdx.x == 0) cn = 0;
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < kWalkUnroll; ++k) {
+    if (ck.u0 + wave + 4 * k >= ck.u1) break;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const uint32_t bits = __float_as_uint(q[k][i]);
+      if (i < a[k].valid && (bits >> 16) == st.prefix) {
+        if constexpr (PREC == IGSP_FP16) atomicAdd(&lds[(bits >> 13) & 7u], 1u);
+        else lds[atomicAdd(&cn, 1u)] = bits;
+      }
+    }
+  }
+  __syncthreads();
+  if constexpr (PREC == IGSP_FP16) {
+    if (threadIdx.x < 8 && lds[threadIdx.x])
+      atomicAdd(&L.rhist[(int64_t)v * kRefineBins + threadIdx.x], lds[threadIdx.x]);
+    return;
+  }
+  const uint32_t n = cn;  // at most the chunk's pixels
+  if (n <= kGatherPlain) {
+    if (threadIdx.x == 0 && n) cbase = atomicAdd(&L.cand_n[v], n);
+    __syncthreads();
+    for (uint32_t k = threadIdx.x; k < n; k += 256) add_candidate(L, vd, v, cbase + k, lds[k], 1u);
+    return;
+  }
+  uint32_t* const keys = lds + kGatherList;  // 0: free (a stored survivor is never 0)
+  uint32_t* const times = keys + kGatherTable;
+  for (int k = threadIdx.x; k < kGatherTable; k += 256) keys[k] = times[k] = 0;
+  __syncthreads();
+  for (uint32_t k = threadIdx.x; k < n; k += 256) {
+    const uint32_t bits = lds[k];
+    uint32_t h = (bits * 2654435761u) >> 22;
+    bool placed = false;
+    for (int probe = 0; probe < 8 && !placed; ++probe) {
+      const uint32_t prev = atomicCAS(&keys[h], 0u, bits);
+      if (prev == 0u || prev == bits) {
+        atomicAdd(&times[h], 1u);
+        placed = true;
+      }
+      h = (h + 1) & (kGatherTable - 1);
+    }
+    if (!placed) add_candidate(L, vd, v, atomicAdd(&L.cand_n[v], 1u), bits, 1u);
+  }
+  __syncthreads();
+  for (int k = threadIdx.x; k < kGatherTable; k += 256)
+    if (keys[k]) add_candidate(L, vd, v, atomicAdd(&L.cand_n[v], 1u), keys[k], times[k]);
+}
+
+// The rest of FP32's selection (16 bits, two digits of 8) by one work-group:
+// from the view's candidate list, or from the stored map where the list had
+// no room (hs: 256 words of LDS).
+__device__ __forceinline__ MedState resolve_view(const EdgeLaunch& L, int v, const ViewDesc& vd, MedState st, uint32_t* hs,
+                                                 uint32_t* tmp, MedState* s_st) {
+  if (st.n == 0) return st;
+  const uint32_t nc = L.cand_n[v];
+  const uint2* list = reinterpret_cast<const uint2*>(L.cand) + vd.cand_off;
+  for (int pass = 0; pass < 2; ++pass) {
+    hs[threadIdx.x] = 0;
+    __syncthreads();
+    const int dshift = st.shift - 8;
+    if (nc <= (uint32_t)vd.cand_cap) {
+      for (uint32_t k = threadIdx.x; k < nc; k += 256) {
+        const uint2 e = list[k];
+        if ((e.x >> st.shift) == st.prefix) atomicAdd(&hs[(e.x >> dshift) & 255u], e.y);
+      }
+    } else {
+      const RowChunk all = {v, 0, strips_of(vd) * vd.H, 0};
+      refine_slots<IGSP_FP32, 4, false>(L, vd, all, st, 8, hs, __lane_id(),
+                                        __builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
+    }
+    __syncthreads();
+    st = refine_step(L, st, hs, 8, tmp, s_st);
+  }
+  return st;
 }
 
 // ------------------------------------------------------------- stage 3
@@ -896,34 +1121,29 @@ __device__ __forceinline__ void normalise4(const float v[4], float med, float in
 }
 
 // Normalisation of one row chunk by NW wavefronts. Each wavefront keeps
-// kNormUnroll slots' loads in flight (slots past the chunk's end load the
+// kUnroll slots' loads in flight (slots past the chunk's end load the
 // last slot again and store nothing). The chunk's output pixels are one
 // contiguous range of the map; a buffer descriptor over it takes a lane's
 // four values in one 16-byte store, and the last lane of a row whose width is
 // not a multiple of 4 stores its pixels one by one (a fourth value would land
 // on the next row).
 template <int PREC, int NW, bool COHERENT>
-__device__ __forceinline__ void norm_slots(const EdgeLaunch& L, const ViewDesc& vd, const RowChunk& ck, float med,
-                                           int lane, int wave) {
-  constexpr int kNormUnroll = COHERENT ? kPersistWalkUnroll : kWalkUnroll;
-  const int ns = strips_of(vd);
-  const float inv = med > 0.0f ? 1.0f / med : 0.0f;
-  // the chunk's output pixels: from its first slot's first pixel to its last
-  // slot's last
-  const int cb = ck.u0 / ns, ce = (ck.u1 - 1) / ns;
-  const int64_t p_begin = (int64_t)cb * vd.W + kStripCols * (ck.u0 - cb * ns);
-  const int64_t p_end = (int64_t)ce * vd.W + min(vd.W, kStripCols * (ck.u1 - ce * ns));
-  const __amdgpu_buffer_rsrc_t out = buffer_rsrc(L.out + vd.out_off + p_begin, (int)(4 * (p_end - p_begin)));
-  for (int u0 = ck.u0 + wave; u0 < ck.u1; u0 += kNormUnroll * NW) {
-    SlotAt a[kNormUnroll];
-    float v[kNormUnroll][4];
+struct NormWalk {
+  static constexpr int kUnroll = COHERENT ? kPersistWalkUnroll : kWalkUnroll;
+  SlotAt a[kUnroll];
+  float v[kUnroll][4];
+
+  __device__ __forceinline__ void load(const EdgeLaunch& L, const ViewDesc& vd, const RowChunk& ck, int ns, int u0, int lane) {
 #pragma unroll
-    for (int k = 0; k < kNormUnroll; ++k) {
+    for (int k = 0; k < kUnroll; ++k) {
       a[k] = view_slot(vd, ns, min(u0 + k * NW, ck.u1 - 1), lane);
       load4<PREC, COHERENT>(L, a[k].stored, v[k]);
     }
+  }
+  __device__ __forceinline__ void store(const RowChunk& ck, int u0, __amdgpu_buffer_rsrc_t out, int64_t p_begin,
+                                        float med, float inv) const {
 #pragma unroll
-    for (int k = 0; k < kNormUnroll; ++k) {
+    for (int k = 0; k < kUnroll; ++k) {
       if (u0 + k * NW >= ck.u1) break;
       float e[4];
       normalise4<PREC>(v[k], med, inv, e);
@@ -938,33 +1158,78 @@ __device__ __forceinline__ void norm_slots(const EdgeLaunch& L, const ViewDesc& 
       }
     }
   }
+};
+
+// The chunk's output pixels, one contiguous range of the map: from its first
+// slot's first pixel to its last slot's last.
+struct ChunkOut {
+  int64_t p_begin;
+  __amdgpu_buffer_rsrc_t out;
+};
+
+__device__ __forceinline__ ChunkOut chunk_out(const EdgeLaunch& L, const ViewDesc& vd, const RowChunk& ck, int ns) {
+  const int cb = ck.u0 / ns, ce = (ck.u1 - 1) / ns;
+  const int64_t p_begin = (int64_t)cb * vd.W + kStripCols * (ck.u0 - cb * ns);
+  const int64_t p_end = (int64_t)ce * vd.W + min(vd.W, kStripCols * (ck.u1 - ce * ns));
+  return {p_begin, buffer_rsrc(L.out + vd.out_off + p_begin, (int)(4 * (p_end - p_begin)))};
 }
 
-// Normalisation of a row chunk. Where the last selection step is folded in
-// (FP32), each work-group takes it itself from the last pass's histogram and
-// the view's first chunk stores the final state and writes the view's
-// outputs; otherwise the final state is read.
-template <int PREC>
+template <int PREC, int NW, bool COHERENT>
+__device__ __forceinline__ void norm_slots(const EdgeLaunch& L, const ViewDesc& vd, const RowChunk& ck, float med,
+                                           int lane, int wave) {
+  using Walk = NormWalk<PREC, NW, COHERENT>;
+  const int ns = strips_of(vd);
+  const float inv = med > 0.0f ? 1.0f / med : 0.0f;
+  const ChunkOut o = chunk_out(L, vd, ck, ns);
+  for (int u0 = ck.u0 + wave; u0 < ck.u1; u0 += Walk::kUnroll * NW) {
+    Walk w;
+    w.load(L, vd, ck, ns, u0, lane);
+    w.store(ck, u0, o.out, o.p_begin, med, inv);
+  }
+}
+
+// Normalisation of a row chunk (of at most kChunkSlots slots: one walk step
+// per wavefront, loaded before the median is known). Each work-group takes
+// the last selection step itself, from the last pass's digit counts (in the
+// short chain FP32's last two, from the candidates), and the view's first
+// chunk stores the final state and writes the view's outputs.
+template <int PREC, bool SHORT>
 __global__ __launch_bounds__(256) void normalise_kernel(EdgeLaunch L, int chunk0) {
   __shared__ uint32_t tmp[4];
   __shared__ MedState s_st;
   constexpr int P = refine_passes(PREC);
   const RowChunk ck = L.chunks[chunk0 + blockIdx.x];
   const int v = ck.view;
+  const int64_t n = L.n_views;
+  const ViewDesc vd = L.views[v];
+  const int ns = strips_of(vd);
+  const int u0 = ck.u0 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  NormWalk<PREC, 4, false> w;
+  w.load(L, vd, ck, ns, u0, __lane_id());
   MedState st;
-  if constexpr (!fold_last_step(PREC)) {
-    st = L.state[(int64_t)P * L.n_views + v];
+  if constexpr (P == 0) {
+    st = load_uniform(L.state + v);
   } else {
-    const int64_t n = L.n_views;
-    st = refine_step(L, L.state[(P - 1) * n + v], L.rhist + ((P - 1) * n + v) * kRefineBins,
-                     refine_digit_bits(PREC), tmp, &s_st);
-    if (ck.u0 == 0 && threadIdx.x == 0) {
-      finish_view(L, v, st);
-      L.state[P * n + v] = st;
+    if constexpr (PREC == IGSP_FP16) {
+      st = refine_step8(load_uniform(L.state + v), as_constant(L.rhist + v * (int64_t)kRefineBins));
+    } else if constexpr (SHORT) {
+      __shared__ uint32_t hs[kRefineBins];
+      st = resolve_view(L, v, vd, load_uniform(L.state + v), hs, tmp, &s_st);
+    } else {
+      st = refine_step(L, load_uniform(L.state + (P - 1) * n + v), L.rhist + ((P - 1) * n + v) * kRefineBins,
+                       refine_digit_bits(PREC), tmp, &s_st);
+    }
+    if (ck.u0 == 0) {
+      if (threadIdx.x == 0) {
+        finish_view(L, v, st);
+        L.state[P * n + v] = st;
+      }
+      if constexpr (SHORT)  // ready for the next call
+        for (int i = threadIdx.x; i < Keys<PREC>::bins; i += 256) L.hist[(int64_t)v * kBinsMax + i] = 0;
     }
   }
-  const ViewDesc vd = L.views[v];
-  norm_slots<PREC, 4, false>(L, vd, ck, st.med, __lane_id(), __builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
+  const ChunkOut o = chunk_out(L, vd, ck, ns);
+  w.store(ck, u0, o.out, o.p_begin, st.med, st.med > 0.0f ? 1.0f / st.med : 0.0f);
 }
 
 // ------------------------------------------------------------- unfused form
@@ -1524,19 +1789,26 @@ hipError_t launch_median_refine(const EdgeLaunch& L, int chunk0, int n_chunks, i
   return hipGetLastError();
 }
 
-hipError_t launch_median_step(const EdgeLaunch& L, int v0, int nv, hipStream_t s) {
-  const int passes = refine_passes(L.precision);
-  if (nv <= 0 || passes == 0 || fold_last_step(L.precision)) return hipSuccess;
-  hipLaunchKernelGGL(median_step_kernel, dim3(nv), dim3(256), 0, s, L, v0, passes);
+hipError_t launch_median_gather(const EdgeLaunch& L, int chunk0, int n_chunks, hipStream_t s) {
+  if (n_chunks <= 0) return hipSuccess;
+  if (L.precision == IGSP_FP16) hipLaunchKernelGGL(median_gather_kernel<IGSP_FP16>, dim3(n_chunks), dim3(256), 0, s, L, chunk0);
+  else hipLaunchKernelGGL(median_gather_kernel<IGSP_FP32>, dim3(n_chunks), dim3(256), 0, s, L, chunk0);
   return hipGetLastError();
 }
 
 hipError_t launch_normalise(const EdgeLaunch& L, int chunk0, int n_chunks, hipStream_t s) {
   if (n_chunks <= 0) return hipSuccess;
+  const dim3 g(n_chunks), b(256);
   switch (L.precision) {
-    case IGSP_FP16: hipLaunchKernelGGL(normalise_kernel<IGSP_FP16>, dim3(n_chunks), dim3(256), 0, s, L, chunk0); break;
-    case IGSP_BF16: hipLaunchKernelGGL(normalise_kernel<IGSP_BF16>, dim3(n_chunks), dim3(256), 0, s, L, chunk0); break;
-    default: hipLaunchKernelGGL(normalise_kernel<IGSP_FP32>, dim3(n_chunks), dim3(256), 0, s, L, chunk0); break;
+    case IGSP_FP16:
+      if (L.short_chain) hipLaunchKernelGGL((normalise_kernel<IGSP_FP16, true>), g, b, 0, s, L, chunk0);
+      else hipLaunchKernelGGL((normalise_kernel<IGSP_FP16, false>), g, b, 0, s, L, chunk0);
+      break;
+    case IGSP_BF16: hipLaunchKernelGGL((normalise_kernel<IGSP_BF16, false>), g, b, 0, s, L, chunk0); break;
+    default:
+      if (L.short_chain) hipLaunchKernelGGL((normalise_kernel<IGSP_FP32, true>), g, b, 0, s, L, chunk0);
+      else hipLaunchKernelGGL((normalise_kernel<IGSP_FP32, false>), g, b, 0, s, L, chunk0);
+      break;
   }
   return hipGetLastError();
 }

@@ -20,11 +20,7 @@
 namespace igsp {
 namespace {
 
-// Slots (248 pixels each) per work-group of the element-wise passes, about
-// 4 Ki pixels (measured best for normalisation), per work-group of the
-// median's refinement passes (coarser: each work-group clears and flushes a
-// histogram) and per element-wise task of the persistent form.
-constexpr int kChunkSlots = 16;
+// Slots (248 pixels each) per element-wise task of the persistent form.
 constexpr int kPersistChunkSlots = 264;
 // Distance, in tasks, between a view's phases in the persistent task list, as
 // a multiple of the resident work-groups: a task handed out that many
@@ -82,6 +78,7 @@ struct EdgeKey {
 struct EdgePlan {
   EdgeKey key;
   int n_views = 0;
+  int seg_rows = 0;  // rows per wavefront segment in the items (key.seg_rows, or less)
   ViewDesc* d_views = nullptr;
   EdgeItem* d_items = nullptr;
   EdgeItem* d_items_all = nullptr;  // the same items in the order of a launch over every view
@@ -138,17 +135,39 @@ int device_cus() {
 // shorter segments then save more time than their extra halo rows cost. The
 // plain form launches each view on its own, so it counts per view. (Each
 // height plus the 8 halo rows is a multiple of the loop's 6-row unroll.)
+constexpr int kShortestSeg = 10;
+
+// Wavefronts of a stencil launch over the views at a segment height.
+int64_t stencil_waves(const igsp_view* views, int32_t n, int seg) {
+  int64_t waves = 0;
+  for (int i = 0; i < n; ++i)
+    waves += (int64_t)((views[i].width + kStripCols - 1) / kStripCols) * ((views[i].height + seg - 1) / seg);
+  return waves;
+}
+
 int default_seg_rows(const igsp_view* views, int32_t n, int form) {
-  static const int kHeights[] = {64, 40, 28, 22, 16, 10};
+  static const int kHeights[] = {64, 40, 28, 22, 16, kShortestSeg};
   const int64_t target = 16 * (int64_t)device_cus();
   for (int seg : kHeights) {
-    int64_t waves = 0;
-    for (int i = 0; i < n; ++i)
-      waves += (int64_t)((views[i].width + kStripCols - 1) / kStripCols) * ((views[i].height + seg - 1) / seg);
+    int64_t waves = stencil_waves(views, n, seg);
     if (form == IGSP_PLAIN && n > 0) waves /= n;
     if (waves >= target) return seg;
   }
-  return kHeights[sizeof(kHeights) / sizeof(kHeights[0]) - 1];
+  return kShortestSeg;
+}
+
+// A plan of the shortest segments whose wavefronts would leave most SIMDs
+// idle splits them once more, to 4 rows (12 with the halo, two rounds of the
+// unroll): a lone wavefront takes 0.48 us a row, and six rows fewer save more
+// than the extra halo rows and histogram flushes cost while no two wavefronts
+// share a SIMD. One FP32 256x192 view (96 wavefronts at 4 rows): 25.1 -> 22.0
+// us; 1297x840 (1260): 32.0 -> 32.8; 40 ragged views (FP16, 1300): 34.0 ->
+// 36.5, so the line is at two wavefronts per CU.
+constexpr int kSplitSeg = 4;
+
+int plan_seg_rows(const igsp_view* views, int32_t n, int seg) {
+  if (seg == kShortestSeg && stencil_waves(views, n, kSplitSeg) <= 2 * (int64_t)device_cus()) return kSplitSeg;
+  return seg;
 }
 
 // ------------------------------------------------------------------ tuning
@@ -265,7 +284,8 @@ igsp_status build_edge_plan(const EdgeKey& key, std::shared_ptr<EdgePlan>* out) 
   plan->key = key;
   const int n = (int)key.views.size();
   plan->n_views = n;
-  const int band = key.seg_rows * key.wg_waves;
+  plan->seg_rows = plan_seg_rows(key.views.data(), n, key.seg_rows);
+  const int band = plan->seg_rows * key.wg_waves;
   const int esz = key.precision == IGSP_FP32 ? 4 : 2;
   std::vector<ViewDesc> vd(n);
   std::vector<EdgeItem> items;
@@ -322,7 +342,7 @@ igsp_status build_edge_plan(const EdgeKey& key, std::shared_ptr<EdgePlan>* out) 
     return IGSP_ERR_HIP;
   if (hipMalloc(&plan->d_map, (size_t)std::max<int64_t>(map_elems, 64) * esz) != hipSuccess) return IGSP_ERR_HIP;
   if (cand_elems > 0 &&
-      (hipMalloc(reinterpret_cast<void**>(&plan->d_cand), (size_t)cand_elems * sizeof(uint32_t)) != hipSuccess ||
+      (hipMalloc(reinterpret_cast<void**>(&plan->d_cand), (size_t)cand_elems * sizeof(uint2)) != hipSuccess ||
        hipMalloc(reinterpret_cast<void**>(&plan->d_cand_n), (size_t)n * sizeof(uint32_t)) != hipSuccess))
     return IGSP_ERR_HIP;
   // refinement histograms of up to two passes, selection states after 0, 1
@@ -480,6 +500,25 @@ igsp_status get_edge_plan(const igsp_view* views, int32_t n_views, const igsp_ed
   return st;
 }
 
+// Whether the stages of views [v0, v1) take the short median chain (FP32,
+// FP16). It saves two (FP32) launches of 4 us, but every work-group then
+// selects from its view's whole first histogram and list: measured about
+// 3 ns a chunk and 1/80 ns more for each chunk of the same view (the list
+// grows with the view), against 8 us saved; FP16 costs and saves half. Short
+// against long, FP32: one 1297x840 view (293 chunks) 32.5 and 37.9 us, two
+// 40.3 and 45.4, four (1180) 54.2 and 52.8, one 2473x1643 (929) 57.4 and
+// 52.0, 64 views of 300x187 (1491) 52.4 and 55.4, 200 of them 95.7 and 89.3;
+// FP16: 27.1 and 29.5, 30.0 and 32.3, 38.3 and 41.6, 44.1 and 41.3, 44.5 and
+// 47.0, 84.3 and 80.9.
+bool short_chain(const EdgePlan& P, int v0, int v1) {
+  int64_t cost = 0;
+  for (int v = v0; v < v1 && cost <= 80 * 8000; ++v) {
+    const int64_t c = P.chunk_begin[v + 1] - P.chunk_begin[v];
+    cost += c * (80 * 3 + c);
+  }
+  return cost <= 80 * 8000;
+}
+
 igsp_status enqueue_edge(EdgePlan* P, const uint8_t* images, int64_t img_end, float* out_maps,
                          const igsp_edge_opts* opts, hipStream_t s) {
   EdgeLaunch L;
@@ -496,6 +535,7 @@ igsp_status enqueue_edge(EdgePlan* P, const uint8_t* images, int64_t img_end, fl
   L.cand = P->d_cand;
   L.cand_n = P->d_cand_n;
   L.use_cand = 0;
+  L.short_chain = 0;
   L.n_views = P->n_views;
   L.medians_dn = opts ? opts->medians : nullptr;
   L.survivors = opts ? opts->survivors : nullptr;
@@ -503,7 +543,7 @@ igsp_status enqueue_edge(EdgePlan* P, const uint8_t* images, int64_t img_end, fl
   L.status = opts ? opts->status : nullptr;
   L.precision = P->key.precision;
   L.wg_waves = P->key.wg_waves;
-  L.seg_rows = P->key.seg_rows;
+  L.seg_rows = P->seg_rows;
   const int form = resolve_form(P->key.views.data(), P->n_views, opts);
   const bool batched = form != IGSP_PLAIN;
   const int n = P->n_views;
@@ -512,8 +552,11 @@ igsp_status enqueue_edge(EdgePlan* P, const uint8_t* images, int64_t img_end, fl
   const int passes = L.precision == IGSP_FP16 ? 1 : (L.precision == IGSP_FP32 ? 2 : 0);
   hipEvent_t* ev = L.stage_events;
   auto mark = [&](int k, hipStream_t st) -> hipError_t { return ev ? hipEventRecord(ev[k], st) : hipSuccess; };
-  // median selection (+ refinement passes) and normalisation of views [v0, v1)
+  auto is_short = [&](int v0, int v1) { return form != IGSP_UNFUSED && passes > 0 && short_chain(*P, v0, v1); };
+  // median selection (+ refinement passes) of views [v0, v1); the last
+  // selection step is taken by the normalisation
   auto tail = [&](int v0, int v1, hipStream_t st) -> hipError_t {
+    if (is_short(v0, v1)) return launch_median_gather(L, P->chunk_begin[v0], P->chunk_begin[v1] - P->chunk_begin[v0], st);
     const int f0 = P->rchunk_begin[v0], f1 = P->rchunk_begin[v1];
     EdgeLaunch LR = L;
     LR.chunks = P->d_rchunks;
@@ -522,22 +565,20 @@ igsp_status enqueue_edge(EdgePlan* P, const uint8_t* images, int64_t img_end, fl
     // than the second pass's bytes: +2% for the plain form, measured)
     LR.use_cand = L.cand && v1 - v0 > 1;
     hipError_t e = launch_median_select(L, v0, v1 - v0, st);
-    // each refinement pass takes the previous pass's selection step itself;
-    // the last one is taken by a launch of its own or by the normalisation
+    // each refinement pass takes the previous pass's selection step itself
     for (int p = 0; p < passes && e == hipSuccess; ++p) e = launch_median_refine(LR, f0, f1 - f0, p, st);
-    if (e == hipSuccess) e = launch_median_step(L, v0, v1 - v0, st);
     return e;
   };
   auto stencil = [&](int v0, int v1, hipStream_t st) -> hipError_t {
-    if (v0 == 0 && v1 == n) {
-      EdgeLaunch LA = L;
-      LA.items = P->d_items_all;
-      return launch_edge_fused(LA, 0, P->item_begin[n], st);
-    }
-    return launch_edge_fused(L, P->item_begin[v0], P->item_begin[v1] - P->item_begin[v0], st);
+    EdgeLaunch LA = L;
+    LA.short_chain = is_short(v0, v1);
+    if (v0 == 0 && v1 == n) LA.items = P->d_items_all;
+    return launch_edge_fused(LA, P->item_begin[v0], P->item_begin[v1] - P->item_begin[v0], st);
   };
   auto norm = [&](int v0, int v1, hipStream_t st) -> hipError_t {
-    return launch_normalise(L, P->chunk_begin[v0], P->chunk_begin[v1] - P->chunk_begin[v0], st);
+    EdgeLaunch LA = L;
+    LA.short_chain = is_short(v0, v1);
+    return launch_normalise(LA, P->chunk_begin[v0], P->chunk_begin[v1] - P->chunk_begin[v0], st);
   };
   hipError_t e = mark(0, s);
   if (e == hipSuccess && form == IGSP_BATCHED_PERSISTENT) {

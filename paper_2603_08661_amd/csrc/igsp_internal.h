@@ -39,6 +39,9 @@ constexpr int kBinsSquare = 58 * 128;                      // 1 .. 2^58
 constexpr int kBinsMax = kBinsSquare;
 constexpr int kRefineBins = 256;          // radix digit of the refine passes
 constexpr int kRefineChunkSlots = 64;     // slots per work-group of a refinement pass
+// Slots (248 pixels each) per work-group of the other element-wise passes,
+// about 4 Ki pixels (measured best for normalisation).
+constexpr int kChunkSlots = 16;
 
 // The stored intermediate of a view is kept strip by strip: strip s (output
 // columns 248 s .. 248 s + 247) holds its rows one after another in slots of
@@ -97,9 +100,11 @@ struct EdgeLaunch {
   uint32_t* hist;            // [n_views][kBinsMax]
   uint32_t* rhist;           // [2][n_views][kRefineBins]: refinement pass p's digit histograms
   MedState* state;           // [3][n_views]: the selection state after p refinement steps
-  uint32_t* cand;            // FP32: survivors in the first histogram's median bucket, per view
+  uint32_t* cand;            // FP32: survivors in the first histogram's median bucket, per view (short chain:
+                             // pairs of value and count)
   uint32_t* cand_n;          // [n_views]: candidates found (more than the room: list not used)
   int use_cand;              // the refinement passes of this launch use the candidate lists
+  int short_chain;           // the median takes one launch (median_gather) before the normalisation
   float* medians_dn;         // optional outputs
   int32_t* survivors;
   hipEvent_t* stage_events;  // optional, 4 events
@@ -178,8 +183,8 @@ struct UfLaunch {
 hipError_t launch_edge_fused(const EdgeLaunch& L, int item0, int n_items, hipStream_t s);
 hipError_t launch_median_select(const EdgeLaunch& L, int v0, int nv, hipStream_t s);
 hipError_t launch_median_refine(const EdgeLaunch& L, int chunk0, int n_chunks, int pass, hipStream_t s);
-// the last selection step where the normalisation does not take it (no-op otherwise)
-hipError_t launch_median_step(const EdgeLaunch& L, int v0, int nv, hipStream_t s);
+// the short chain's only launch between the stencil and the normalisation
+hipError_t launch_median_gather(const EdgeLaunch& L, int chunk0, int n_chunks, hipStream_t s);
 hipError_t launch_normalise(const EdgeLaunch& L, int chunk0, int n_chunks, hipStream_t s);
 // The stencil steps of the unfused form: gray, blur, Sobel, suppression
 // (+ histogram), four launches; the median and normalisation follow as in the

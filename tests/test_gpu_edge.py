@@ -227,3 +227,36 @@ def test_fp32_median_candidates_overflow_and_fit(form):
     assert counts[0] > room >= counts[1], (counts, room)
     vb = synth.pack_views([stripes, textured, stripes], in_align=3, out_align=2)
     check_batch(vb, "fp32", form)
+
+
+@pytest.mark.parametrize("form", ["plain", "staged"])
+def test_fp32_candidate_list_without_room(form):
+    """The short chain lists the median bucket's values with their counts
+    (room: 1/16 of the view's pixels, at least 256). Stripes with one grey
+    level of noise give more distinct values in that bucket than there is
+    room for, so the selection reads the map; the view beside them has plain
+    stripes (many survivors, few values) and lists them."""
+    H, W = 64, 600
+    flat = np.zeros((H, W, 3), np.uint8)
+    flat[:] = ((((np.arange(W) // 3) % 2) * 180) + 30).astype(np.uint8)[None, :, None]
+    noisy = flat + np.random.default_rng(5).integers(0, 2, flat.shape).astype(np.uint8)
+    distinct = []
+    for im in (flat, noisy):
+        o = oracle.edge_view(im)
+        bits = o["M"][o["keep"].astype(bool)].astype(np.float32).view(np.uint32)
+        med = np.float32(o["Mmed"]).view(np.uint32)
+        distinct.append(np.unique(bits[(bits >> 16) == (med >> 16)]).size)
+    assert distinct[0] < 64 and distinct[1] > H * W // 16, distinct
+    check_batch(synth.pack_views([noisy, flat, noisy], in_align=1, out_align=2), "fp32", form, reps=2)
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp16"])
+@pytest.mark.parametrize("rows", [1376, 1377])
+def test_short_and_long_median_chain(precision, rows):
+    """688 element-wise chunks (8 strips x 1376 rows, 16 slots each) are the
+    most the short chain takes of one view; one row more takes the long one.
+    Both equal the unfused form, which always takes the long one, bit for bit."""
+    vb = synth.pack_views([synth.image(61, 1984, rows, n_poly=20, texture=True)], in_align=16, out_align=4)
+    a, ma, na = gpu_edge(vb, precision, "staged", reps=2)
+    b, mb, nb = gpu_edge(vb, precision, "unfused")
+    assert np.array_equal(a, b) and np.array_equal(ma, mb) and np.array_equal(na, nb) and na[0] > 0
