@@ -199,15 +199,14 @@ def summarise_profile(d: str, copy_bytes: int):
         fetch_rows = _csv_rows(os.path.join(d, "fetch", "**", "*counter_collection.csv"))
         write_rows = _csv_rows(os.path.join(d, "write", "**", "*counter_collection.csv"))
         npx = res["config"]["megapixels"] * 1e6
-        alg = {f"normalise_kernel<{prec_code}>": npx * (STORE_BYTES[res["config"]["intermediate"]] + 4)}
+        alg = {f"normalise_kernel<{prec_code}, false>": npx * (STORE_BYTES[res["config"]["intermediate"]] + 4)}
         t += ["", "Other kernels, same passes and scaling (MB per dispatch; algorithmic bytes where the "
                   "benchmark states them per kernel). The plain split and the full-record split (feature rows and "
                   "moments) are separate kernels:", "",
               "| Kernel | Dispatches | Fetch | Write | Traffic | Algorithmic |", "|---|---|---|---|---|---|"]
-        for k in (f"normalise_kernel<{prec_code}>", f"median_select_kernel<{prec_code}>", "las_count_kernel",
+        for k in (f"normalise_kernel<{prec_code}, false>", f"median_select_kernel<{prec_code}>", "las_count_kernel",
                   "las_scan_kernel", "las_split_kernel", "las_split_full_kernel", "sel_scatter_kernel",
-                  "sel_compact_kernel",
-                  "sel_hist_kernel", "sel_mask_kernel"):
+                  "sel_hist_kernel", "sel_collect_kernel"):
             fv = [float(r["Counter_Value"]) * 1024 * f_fetch for r in fetch_rows
                   if k in r["Kernel_Name"] and r["Counter_Name"] == "FETCH_SIZE"]
             wv = [float(r["Counter_Value"]) * 1024 * f_write for r in write_rows
@@ -486,7 +485,10 @@ def main():
             igsp.split_mask(out, views, cg, cv, cp, cw, tg, scount, smask, sscore, grad_threshold=thr,
                             budget=N0 + K, n_selected=snsel, stream=stream)
         sms, _ = timed(run_select, 1, 5)
-        sbytes = 28 * cb.n + 133 * N0
+        # 16 B of entry, 4 B of map and about 8 B of score traffic per
+        # contribution; per row 8 cleared, 16 of score additions, 12 read by
+        # each of two passes, 1 of mask
+        sbytes = 28 * cb.n + 49 * N0
         select = {"contributions": cb.n, "order": args.contrib_order, "gaussians": N0,
                   "selected": int(snsel.item()), "ms": round(sms, 4),
                   "contributions_per_s": round(cb.n / (sms * 1e-3), 1),

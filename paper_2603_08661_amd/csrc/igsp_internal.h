@@ -243,27 +243,22 @@ struct SelView {
   int64_t pixels;      // width * height
 };
 
-struct SelState {      // device scalars of one selection
-  uint64_t prefix;     // resolved high bits of the K-th largest key
-  uint64_t kth;        // the K-th largest key (valid once shift == 0)
-  int64_t rank;        // rank inside the prefix group, from the top; at the
-                       // end: the ties at kth still to take
-  int64_t k;           // Gaussians to select
-  int64_t candidates;
-  int64_t ties;
-  uint64_t top;        // bitwise OR of the candidates' keys
-  int32_t shift;       // low bits still unresolved
-  int32_t pad;
-};
+// Bins of the keys' first histogram: 128 exact small keys, then 64 for each
+// of the 57 larger exponents, rounded up to whole words per thread.
+constexpr int kSelBins = 4096;
+constexpr int kSelHistGrid = 512;      // its work-groups (each clears and flushes a histogram)
 
-struct SelRadix {      // the selection after one radix pass
-  uint64_t prefix;
-  int64_t rank;
-  int32_t shift;
-  int32_t pad;
-};
+enum : int32_t { kSelDone = 0, kSelList = 1, kSelTie = 2 };
 
-constexpr int kSelPasses = 8;  // 8-bit digits of a 64-bit key
+struct SelState {      // device scalars of one selection, after sel_collect
+  int64_t need;        // rows of the K-th key's bin to take
+  int64_t last;        // kSelTie: the last row taken
+  int32_t bin;
+  int32_t mode;        // kSelDone: the bin is taken whole; kSelList: its rows are listed;
+                       // kSelTie: they share one key, counted per tile
+  uint32_t listed;
+  uint32_t pad;
+};
 
 struct SelLaunch {
   const float* maps;
@@ -283,11 +278,10 @@ struct SelLaunch {
   uint8_t* mask;
   int64_t* scores;
   int64_t* n_selected;
-  uint32_t* hist;           // [3][256]: pass p adds into slot p % 3, reads p - 1's
-  SelRadix* ring;           // [2]: the selection after pass p in slot p % 2
-  uint64_t* ckeys;          // [capacity]: the candidates' keys, in row order
+  uint32_t* hist;           // [kSelBins]
+  uint64_t* ckeys;          // [capacity]: keys and rows of the K-th key's bin, in any order
+  int32_t* crows;
   uint32_t* tile_counts;    // [tiles]
-  int64_t* tile_offsets;    // [tiles]
   SelState* state;
   int grid;
 };

@@ -11,19 +11,16 @@
 //                 adds each sum with one 64-bit atomic; fixed
 //                 point makes the sum exact and independent of the order
 //                 the additions land in
-//   sel_count<0> / sel_scan<0> : candidates (warm-up, or grad[g] >=
-//                 threshold) per tile, their offsets, and
-//                 K = min(candidates, max(0, budget - N))
-//   sel_compact : the candidates' keys (score + 1) packed in row order, and
-//                 the OR of them (the highest digit any of them uses)
-//   sel_hist    : exact radix selection, 8 bits at a time from the highest
-//                 used digit, of the K-th largest key among the packed keys;
-//                 each pass first resolves the previous pass's digit from
-//                 that pass's histogram (every work-group alike), so no
-//                 separate launch picks the digit
-//   sel_count<1> / sel_scan<1> / sel_mask : the last digit, then ties at the
-//                 K-th key taken in ascending index order (per-tile counts,
-//                 one scan, write)
+//   sel_hist    : the candidates' keys (score + 1) counted by their leading
+//                 bits: exponent and 6 more, so keys below 128 exactly
+//   sel_collect : every work-group finds K = min(candidates, max(0, budget -
+//                 N)) and the bin of the K-th largest key from that histogram;
+//                 rows above the bin are selected, rows inside it listed (or,
+//                 where the bin is one exact key shared by more rows than are
+//                 still to take, counted per tile)
+//   sel_finish  : one work-group: exact selection among the listed keys, ties
+//                 by lower index; or the last row of a tie from the tile counts
+//   sel_ties    : the rows of such a tie (nothing to do otherwise)
 #include "igsp_internal.h"
 
 namespace igsp {
@@ -47,22 +44,24 @@ __global__ __launch_bounds__(kSelThreads) void sel_clear_kernel(SelLaunch S) {
   for (int64_t g = (int64_t)blockIdx.x * kSelThreads + threadIdx.x; g < N; g += (int64_t)gridDim.x * kSelThreads)
     S.scores[g] = 0;
   if (blockIdx.x == 0) {
-    for (int i = threadIdx.x; i < 3 * 256; i += kSelThreads) S.hist[i] = 0;
-    if (threadIdx.x == 0) S.state->top = 0;
+    for (int i = threadIdx.x; i < kSelBins; i += kSelThreads) S.hist[i] = 0;
+    if (threadIdx.x == 0) S.state->listed = 0;
   }
 }
 
 // Contributions arrive in image order, so neighbouring entries often name the
 // same Gaussian, and a Gaussian's entries recur a few image rows later. The
-// grid sweeps the list in order, one chunk of kScatterRounds x kSelThreads
+// grid sweeps the list in order, one chunk of `rounds` x kSelThreads
 // contributions per work-group at a time (so the map reads of neighbouring
 // chunks stay close). Each wavefront first sums the runs of equal Gaussian
-// index on consecutive lanes (a segmented suffix sum over the lanes); a run's
+// index on consecutive lanes (a prefix sum over the lanes by DPP, whose
+// difference over a run is exact modulo 2^64; a segmented sum by shuffles
+// kept the LDS pipe busy with 18 of them a round: 3.5M entries 30.7 -> 26.6 us;
+// 106M, bound by memory, the same); a run's
 // first lane then adds the run's sum into the work-group's LDS hash table
 // (open addressing, kScatterProbes linear probes; a run that finds no slot
 // goes straight to its global atomic); at the end of the chunk every used
 // slot issues one 64-bit atomic and is cleared.
-constexpr int kScatterRounds = 16;
 constexpr int kScatterSlots = 1024;  // 12 KB of LDS: keys and 64-bit sums
 constexpr int kScatterProbes = 16;
 static_assert(kScatterSlots == 1 << 10, "the slot hash keeps the top 10 bits");
@@ -71,12 +70,36 @@ static_assert(kScatterSlots == 1 << 10, "the slot hash keeps the top 10 bits");
 // contribution's map read waits on one global load fewer.
 constexpr int kSelLdsViews = 512;  // at most this many views go to LDS (8 KB)
 
-template <bool LDS_VIEWS>
-__global__ __launch_bounds__(kSelThreads) void sel_scatter_kernel(SelLaunch S) {
+// Inclusive sum over a wavefront's lanes (mod 2^64).
+__device__ __forceinline__ uint64_t wave_incl_sum(uint64_t v) {
+#define IGSP_SUM_STEP(ctrl, rows)                                                                  \
+  {                                                                                                \
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, ctrl, rows, 0xf, false);          \
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(v >> 32), ctrl, rows, 0xf, false);  \
+    v += ((uint64_t)hi << 32) | lo;                                                                \
+  }
+  IGSP_SUM_STEP(0x111, 0xf)  // row_shr:1
+  IGSP_SUM_STEP(0x112, 0xf)  // row_shr:2
+  IGSP_SUM_STEP(0x114, 0xf)  // row_shr:4
+  IGSP_SUM_STEP(0x118, 0xf)  // row_shr:8
+  IGSP_SUM_STEP(0x142, 0xa)  // row_bcast:15 into rows 1 and 3
+  IGSP_SUM_STEP(0x143, 0xc)  // row_bcast:31 into rows 2 and 3
+#undef IGSP_SUM_STEP
+  return v;
+}
+
+template <class T, bool NT>
+__device__ __forceinline__ T stream_load(const T* p) {
+  if constexpr (NT) return __builtin_nontemporal_load(p);
+  else return *p;
+}
+
+template <bool LDS_VIEWS, bool NT>
+__global__ __launch_bounds__(kSelThreads) void sel_scatter_kernel(SelLaunch S, int rounds) {
   __shared__ int32_t keys[kScatterSlots];
   __shared__ unsigned long long sums[kScatterSlots];
   extern __shared__ SelView lviews[];
-  constexpr int64_t kChunk = (int64_t)kScatterRounds * kSelThreads;
+  const int64_t chunk = (int64_t)rounds * kSelThreads;
   const int64_t N = live_count(S);
   const int lane = threadIdx.x & 63;
   for (int i = threadIdx.x; i < kScatterSlots; i += kSelThreads) {
@@ -86,15 +109,18 @@ __global__ __launch_bounds__(kSelThreads) void sel_scatter_kernel(SelLaunch S) {
   if constexpr (LDS_VIEWS)
     for (int i = threadIdx.x; i < S.n_views; i += kSelThreads) lviews[i] = S.views[i];
   __syncthreads();
-  for (int64_t b0 = (int64_t)blockIdx.x * kChunk; b0 < S.n_contrib; b0 += (int64_t)gridDim.x * kChunk) {
-    const int64_t b1 = b0 + kChunk < S.n_contrib ? b0 + kChunk : S.n_contrib;
+  for (int64_t b0 = (int64_t)blockIdx.x * chunk; b0 < S.n_contrib; b0 += (int64_t)gridDim.x * chunk) {
+    const int64_t b1 = b0 + chunk < S.n_contrib ? b0 + chunk : S.n_contrib;
     // software pipeline over the chunk's rounds: while round r's values are
     // scattered, round r + 1's map value and round r + 2's entries are in
     // flight (entries past the chunk read as ignored)
     auto load_entry = [&](int64_t c, int32_t& gi, int32_t& v, int32_t& p, float& w) {
       gi = -1;
       if (c < b1) {
-        gi = S.gauss[c]; v = S.view[c]; p = S.pixel[c]; w = S.weight[c];
+        gi = stream_load<int32_t, NT>(S.gauss + c);
+        v = stream_load<int32_t, NT>(S.view + c);
+        p = stream_load<int32_t, NT>(S.pixel + c);
+        w = stream_load<float, NT>(S.weight + c);
       }
     };
     // the contribution's map value (0 for an ignored entry) and its Gaussian (-1)
@@ -121,16 +147,15 @@ __global__ __launch_bounds__(kSelThreads) void sel_scatter_kernel(SelLaunch S) {
       load_entry(c0 + 2 * kSelThreads + threadIdx.x, gi2, v2, p2, w2);    // round r + 2
       uint64_t q = 0;
       if (e > 0.0f) q = (uint64_t)floorf(e * 4294967296.0f);               // exact: a power-of-two scale
-      const int32_t gp = __shfl_up(g, 1, 64);
+      int32_t gp = __builtin_amdgcn_mov_dpp(g, 0x138, 0xf, 0xf, true);     // wave_shr:1
+      asm volatile("" : "+v"(gp));  // kept a plain move (a wave shift folded into its use is not exact here)
       const bool head = lane == 0 || gp != g;
       const uint64_t heads = __ballot(head);
-      const int rid = __popcll(heads & ((2ull << lane) - 1ull));        // run of this lane
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const uint64_t qo = __shfl_down(q, o, 64);
-        const int ro = __shfl_down(rid, o, 64);
-        if (lane + o < 64 && ro == rid) q += qo;
-      }
+      const uint64_t incl = wave_incl_sum(q), excl = incl - q;
+      // the run's last lane: the one before the next head
+      const uint64_t later = (heads >> lane) >> 1;
+      const int last = later ? lane + __builtin_ctzll(later) : 63;
+      q = (uint64_t)__shfl((unsigned long long)incl, last, 64) - excl;
       if (head && g >= 0 && q != 0) {
         uint32_t h = ((uint32_t)g * 2654435761u) >> (32 - 10);         // 10 bits: kScatterSlots
         bool placed = false;
@@ -182,225 +207,345 @@ __device__ __forceinline__ uint32_t sel_scan(uint32_t v, uint32_t* wsum, uint32_
   return before + x - v;
 }
 
-__device__ __forceinline__ void radix_pick(const uint32_t* cnt, SelRadix& r, uint32_t* wsum, int64_t* pick);
+// Bin of a key by its leading bits (monotone): keys below 128 by themselves,
+// larger ones by exponent and the 6 bits after the leading one.
+__device__ __forceinline__ int key_bin(uint64_t key) {
+  const int e = 63 - __clzll((long long)(key | 1ull));
+  return e <= 6 ? (int)key : (e - 5) * 64 + (int)((key >> (e - 6)) & 63u);
+}
+// Low bits of the keys of a bin that the bin leaves open (0: one exact key).
+__device__ __forceinline__ int open_bits(int bin) { return bin < 128 ? 0 : bin / 64 - 1; }
 
-// Per tile of kSelTile rows: candidates (mode 0) or keys equal to the
-// selected K-th key (mode 1, which first resolves the last digit from the
-// last radix pass's histogram; work-group 0 records the result).
-template <int MODE>
-__global__ __launch_bounds__(kSelThreads) void sel_count_kernel(SelLaunch S) {
-  __shared__ uint32_t wsum[kSelThreads / 64];
-  __shared__ int64_t pick[2];
-  const int64_t N = live_count(S);
-  const int nt = (int)((N + kSelTile - 1) / kSelTile);
-  uint64_t T = 0;
-  if (MODE == 1) {
-    SelRadix r = S.ring[(kSelPasses - 1) & 1];
-    if (r.shift > 0) radix_pick(S.hist + ((kSelPasses - 1) % 3) * 256, r, wsum, pick);
-    T = r.prefix;  // every digit resolved: the K-th largest key (0 when K = 0)
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-      S.state->prefix = r.prefix;
-      S.state->kth = r.prefix;
-      S.state->rank = r.rank;
-      S.state->shift = r.shift;
-    }
+// Rows' keys in flight per thread in the row passes: independent loads, a
+// row's two arrays each.
+constexpr int kSelUnroll = 8;
+static_assert(kSelTile == kSelUnroll * kSelThreads, "one step per tile");
+
+__device__ __forceinline__ void tile_keys(const SelLaunch& S, int64_t t, int64_t N, uint64_t key[kSelUnroll]) {
+  float gr[kSelUnroll];
+  int64_t sc[kSelUnroll];
+#pragma unroll
+  for (int k = 0; k < kSelUnroll; ++k) {
+    const int64_t g = min(t * kSelTile + k * kSelThreads + threadIdx.x, N - 1);  // (past the end: the last row, dropped below)
+    gr[k] = S.grad[g];
+    sc[k] = S.scores[g];
   }
-  for (int t = blockIdx.x; t < nt; t += gridDim.x) {
-    uint32_t c = 0;
-    for (int k = 0; k < kSelTile / kSelThreads; ++k) {
-      const int64_t g = (int64_t)t * kSelTile + k * kSelThreads + threadIdx.x;
-      if (g < N) c += MODE == 0 ? (candidate(S, g) ? 1u : 0u) : (key_of(S, g) == T ? 1u : 0u);
-    }
-    uint32_t total = 0;
-    (void)sel_scan(c, wsum, total);
-    if (threadIdx.x == 0) S.tile_counts[t] = total;
+#pragma unroll
+  for (int k = 0; k < kSelUnroll; ++k) {
+    const int64_t g = t * kSelTile + k * kSelThreads + threadIdx.x;
+    key[k] = g < N && (S.warmup || gr[k] >= S.grad_threshold) ? (uint64_t)sc[k] + 1ull : 0ull;
   }
 }
 
-// One work-group: exclusive scan of the tile counts; mode 0 derives K and
-// starts the selection, mode 1 turns the tie counts into tie ranks.
-template <int MODE>
-__global__ __launch_bounds__(1024) void sel_scan_kernel(SelLaunch S) {
-  __shared__ int64_t wsum[16];
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+// The candidates' keys counted by bin.
+__global__ __launch_bounds__(kSelThreads) void sel_hist_kernel(SelLaunch S) {
+  __shared__ uint32_t h[kSelBins];
   const int64_t N = live_count(S);
-  const int nt = (int)((N + kSelTile - 1) / kSelTile);
-  const int per = (nt + 1023) / 1024;
-  const int t0 = tid * per;
-  int64_t v = 0;
-  for (int k = 0; k < per; ++k)
-    if (t0 + k < nt) v += S.tile_counts[t0 + k];
-  int64_t x = v;
+  const int64_t nt = (N + kSelTile - 1) / kSelTile;
+  if ((int64_t)blockIdx.x >= nt) return;
+  for (int i = threadIdx.x; i < kSelBins; i += kSelThreads) h[i] = 0;
+  __syncthreads();
+  for (int64_t t = blockIdx.x; t < nt; t += gridDim.x) {
+    uint64_t key[kSelUnroll];
+    tile_keys(S, t, N, key);
+#pragma unroll
+    for (int k = 0; k < kSelUnroll; ++k)
+      if (key[k]) atomicAdd(&h[key_bin(key[k])], 1u);
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < kSelBins; i += kSelThreads) {
+    const uint32_t c = h[i];
+    if (c) atomicAdd(&S.hist[i], c);
+  }
+}
+
+// What is left to select once the first histogram is known; every work-group
+// of sel_collect takes this step alike.
+struct SelPick {
+  int64_t k;       // Gaussians to select
+  int64_t need;    // of them, inside the bin
+  int64_t in_bin;  // candidates inside the bin
+  int bin;
+};
+
+__device__ __forceinline__ SelPick pick_bin(const SelLaunch& S, int64_t N, uint32_t* wsum, SelPick* s_pick) {
+  constexpr int PER = kSelBins / kSelThreads;
+  static_assert(kSelBins % kSelThreads == 0 && PER % 4 == 0, "whole 16-byte words of bins per thread");
+  // descending order: thread t holds the bins from kSelBins - 1 - t PER down
+  uint32_t c[PER];
+  const int lo = kSelBins - (threadIdx.x + 1) * PER;
+  uint32_t sum = 0;
+#pragma unroll
+  for (int j = 0; j < PER / 4; ++j) {
+    const uint4 q = reinterpret_cast<const uint4*>(S.hist + lo)[j];
+    c[4 * j] = q.x; c[4 * j + 1] = q.y; c[4 * j + 2] = q.z; c[4 * j + 3] = q.w;
+    sum += q.x + q.y + q.z + q.w;
+  }
+  uint32_t total = 0;
+  int64_t above = sel_scan(sum, wsum, total);
+  const int64_t room = S.budget > N ? S.budget - N : 0;
+  const int64_t K = (int64_t)total < room ? (int64_t)total : room;
+  if (K == 0) {
+    if (threadIdx.x == 0) *s_pick = SelPick{0, 0, 0, kSelBins};
+  } else if (above < K && K <= above + sum) {
+    int bin = lo;
+    uint32_t in = 0;
+    int64_t up = above;
+#pragma unroll
+    for (int j = PER - 1; j >= 0; --j) {
+      if (up + c[j] >= K) { bin = lo + j; in = c[j]; break; }
+      up += c[j];
+    }
+    *s_pick = SelPick{K, K - up, in, bin};
+  }
+  __syncthreads();
+  return *s_pick;
+}
+
+// LDS list of a tile's rows inside the bin.
+__global__ __launch_bounds__(kSelThreads) void sel_collect_kernel(SelLaunch S) {
+  __shared__ uint32_t wsum[kSelThreads / 64];
+  __shared__ SelPick s_pick;
+  __shared__ uint64_t lkey[kSelTile];
+  __shared__ int32_t lrow[kSelTile];
+  __shared__ uint32_t ln, lbase;
+  const int64_t N = live_count(S);
+  const int64_t nt = (N + kSelTile - 1) / kSelTile;
+  if ((int64_t)blockIdx.x >= nt && blockIdx.x > 0) return;
+  const SelPick p = pick_bin(S, N, wsum, &s_pick);
+  const bool all = p.need == p.in_bin;                    // the whole bin (or nothing) is taken
+  const bool tie = !all && open_bits(p.bin) == 0;         // some of the rows of one key
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    S.state->need = p.need;
+    S.state->bin = p.bin;
+    S.state->mode = all ? kSelDone : (tie ? kSelTie : kSelList);
+    if (S.n_selected) *S.n_selected = p.k;
+  }
+  const int least = all ? p.bin : p.bin + 1;              // bins selected as a whole
+  if (threadIdx.x == 0) ln = 0;
+  __syncthreads();
+  for (int64_t t = blockIdx.x; t < nt; t += gridDim.x) {
+    uint64_t key[kSelUnroll];
+    tile_keys(S, t, N, key);
+    uint32_t ties = 0;
+#pragma unroll
+    for (int k = 0; k < kSelUnroll; ++k) {
+      const int r = k * kSelThreads + threadIdx.x;
+      const int64_t g = t * kSelTile + r;
+      const int bin = key[k] ? key_bin(key[k]) : -1;
+      if (g < N) S.mask[g] = (uint8_t)(bin >= least);
+      if (!all && bin == p.bin) {
+        if (tie) {
+          ++ties;
+        } else {
+          const uint32_t at = atomicAdd(&ln, 1u);
+          lkey[at] = key[k];
+          lrow[at] = (int32_t)g;
+        }
+      }
+    }
+    if (all) continue;  // uniform
+    if (tie) {
+      uint32_t total = 0;
+      (void)sel_scan(ties, wsum, total);
+      if (threadIdx.x == 0) S.tile_counts[t] = total;
+      continue;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0 && ln) lbase = atomicAdd(&S.state->listed, ln);
+    __syncthreads();
+    const uint32_t n = ln;
+    for (uint32_t i = threadIdx.x; i < n; i += kSelThreads) {
+      S.ckeys[lbase + i] = lkey[i];
+      S.crows[lbase + i] = lrow[i];
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) ln = 0;
+    __syncthreads();
+  }
+}
+
+// One work-group of kFinThreads threads. A digit of kFinBits bits per pass.
+constexpr int kFinThreads = 1024;
+constexpr int kFinBits = 11;
+constexpr int kFinBins = 1 << kFinBits;
+static_assert(kFinBins == 2 * kFinThreads, "two bins per thread");
+
+// Exclusive sum over the work-group's threads.
+__device__ __forceinline__ uint32_t fin_scan(uint32_t v, uint32_t* wsum) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  uint32_t x = v;
 #pragma unroll
   for (int o = 1; o < 64; o <<= 1) {
-    const int64_t y = __shfl_up(x, o, 64);
+    const uint32_t y = __shfl_up(x, o, 64);
     if (lane >= o) x += y;
   }
   if (lane == 63) wsum[w] = x;
   __syncthreads();
-  int64_t run = 0, total = 0;
-  for (int k = 0; k < 16; ++k) {
-    if (k < w) run += wsum[k];
-    total += wsum[k];
-  }
-  run += x - v;
-  for (int k = 0; k < per; ++k)
-    if (t0 + k < nt) {
-      S.tile_offsets[t0 + k] = run;
-      run += S.tile_counts[t0 + k];
-    }
-  if (tid == 0) {
-    SelState* st = S.state;
-    if (MODE == 0) {
-      const int64_t room = S.budget > N ? S.budget - N : 0;
-      const int64_t K = total < room ? total : room;
-      st->candidates = total;
-      st->k = K;
-      st->prefix = 0;
-      st->rank = K;          // the K-th largest key: K - 1 keys above it
-      st->shift = 64;
-      st->kth = 0;           // (the radix passes keep their progress in the ring)
-      if (S.n_selected) *S.n_selected = K;
-    } else {
-      st->ties = total;
-    }
-  }
-}
-
-// Packs the candidates' keys in row order (tile offsets from sel_scan<0>)
-// and ORs them into the state: the highest set bit of the OR bounds every
-// candidate key, so the radix passes start at the highest digit in use.
-__global__ __launch_bounds__(kSelThreads) void sel_compact_kernel(SelLaunch S) {
-  __shared__ uint32_t wsum[kSelThreads / 64];
-  __shared__ uint64_t wor[kSelThreads / 64];
-  const int64_t N = live_count(S);
-  const int nt = (int)((N + kSelTile - 1) / kSelTile);
-  uint64_t acc = 0;
-  for (int t = blockIdx.x; t < nt; t += gridDim.x) {
-    int64_t before = S.tile_offsets[t];
-    for (int k = 0; k < kSelTile / kSelThreads; ++k) {
-      const int64_t g = (int64_t)t * kSelTile + k * kSelThreads + threadIdx.x;
-      const bool cand = g < N && candidate(S, g);
-      const uint64_t key = cand ? (uint64_t)S.scores[g] + 1ull : 0ull;
-      uint32_t total = 0;
-      const uint32_t r = sel_scan(cand ? 1u : 0u, wsum, total);
-      if (cand) S.ckeys[before + r] = key;
-      acc |= key;
-      before += total;
-    }
-  }
+  uint32_t before = 0;
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) acc |= __shfl_xor(acc, o, 64);
-  if ((threadIdx.x & 63) == 0) wor[threadIdx.x >> 6] = acc;
+  for (int k = 0; k < kFinThreads / 64; ++k) before += k < w ? wsum[k] : 0;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    uint64_t a = 0;
-    for (int w = 0; w < kSelThreads / 64; ++w) a |= wor[w];
-    if (a) atomicOr(reinterpret_cast<unsigned long long*>(&S.state->top), (unsigned long long)a);
-  }
+  return before + x - v;
 }
 
-// Resolves the digit of a radix pass from its histogram cnt[256] (all
-// threads of the work-group take part): the largest digit d whose keys and
-// those of all higher digits number at least the rank; the rank becomes the
-// rank inside digit d. Suffix sums come from a scan over the digits in
-// descending order (thread t holds digit 255 - t).
-__device__ __forceinline__ void radix_pick(const uint32_t* cnt, SelRadix& r, uint32_t* wsum, int64_t* pick) {
-  const int t = threadIdx.x, d = 255 - t;
-  const uint32_t c = cnt[d];
-  uint32_t total = 0;
-  const uint64_t above = sel_scan(c, wsum, total);   // keys of digits > d
-  const uint64_t upto = above + c;                   // keys of digits >= d
-  if ((int64_t)above < r.rank && ((int64_t)upto >= r.rank || d == 0)) {
-    pick[0] = d;
-    pick[1] = r.rank - (int64_t)above;
+// One radix pass over the n listed entries that match(i): their digit(i)
+// counted, then the digit that holds rank `need` found, from the top
+// (DESCENDING) or from the bottom. On return `need` is the rank inside that
+// digit and `in` its entries.
+template <bool DESCENDING, class Match, class Digit>
+__device__ __forceinline__ uint32_t fin_pass(uint32_t n, Match match, Digit digit, int64_t& need, uint32_t& in,
+                                             uint32_t* h, uint32_t* wsum, int64_t* pick) {
+  h[threadIdx.x] = h[threadIdx.x + kFinThreads] = 0;
+  __syncthreads();
+  for (uint32_t i = threadIdx.x; i < n; i += kFinThreads)
+    if (match(i)) atomicAdd(&h[digit(i)], 1u);
+  __syncthreads();
+  const int d0 = DESCENDING ? kFinBins - 1 - 2 * (int)threadIdx.x : 2 * (int)threadIdx.x;
+  const int d1 = DESCENDING ? d0 - 1 : d0 + 1;
+  const uint32_t c0 = h[d0], c1 = h[d1];
+  const int64_t before = fin_scan(c0 + c1, wsum);
+  if (before < need && need <= before + c0 + c1) {
+    const bool second = need > before + c0;
+    pick[0] = second ? d1 : d0;
+    pick[1] = need - before - (second ? c0 : 0);
+    pick[2] = second ? c1 : c0;
   }
   __syncthreads();
-  r.prefix = (r.prefix << 8) | (uint64_t)pick[0];
-  r.rank = pick[1];
-  r.shift -= 8;
+  const uint32_t d = (uint32_t)pick[0];
+  need = pick[1];
+  in = (uint32_t)pick[2];
   __syncthreads();
+  return d;
 }
 
-// Radix pass `pass`: resolve the previous pass's digit (pass 0: the highest
-// digit in use), then count the next digit of the packed keys whose
-// resolved high bits equal the prefix. Work-group 0 records the selection
-// for the next pass and clears the histogram slot the pass after next
-// adds into (last read by the pass before this one).
-__global__ __launch_bounds__(kSelThreads) void sel_hist_kernel(SelLaunch S, int pass) {
-  __shared__ uint32_t h[256];
-  __shared__ uint32_t wsum[kSelThreads / 64];
-  __shared__ int64_t pick[2];
-  SelRadix r;
-  if (pass == 0) {
-    const SelState st = *S.state;
-    const int bits = st.top ? 64 - __clzll((long long)st.top) : 0;
-    r = SelRadix{0ull, st.k, st.k > 0 ? (bits + 7) / 8 * 8 : 0, 0};
-  } else {
-    r = S.ring[(pass - 1) & 1];
-    if (r.shift > 0) radix_pick(S.hist + ((pass - 1) % 3) * 256, r, wsum, pick);
-  }
-  if (blockIdx.x == 0) {
-    if (threadIdx.x == 0) S.ring[pass & 1] = r;
-    if (pass >= 2) S.hist[((pass + 1) % 3) * 256 + threadIdx.x] = 0;
-  }
-  if (r.shift == 0) return;  // nothing to select, or resolved
-  h[threadIdx.x] = 0;
-  __syncthreads();
-  const int64_t n = S.state->candidates;
-  const int shift = r.shift - 8;
-  for (int64_t c = (int64_t)blockIdx.x * kSelThreads + threadIdx.x; c < n; c += (int64_t)gridDim.x * kSelThreads) {
-    const uint64_t key = S.ckeys[c];
-    if (r.shift == 64 || (key >> r.shift) == r.prefix) atomicAdd(&h[(key >> shift) & 255u], 1u);
-  }
-  __syncthreads();
-  const uint32_t cnt = h[threadIdx.x];
-  if (cnt) atomicAdd(&S.hist[(pass % 3) * 256 + threadIdx.x], cnt);
-}
-
-__global__ __launch_bounds__(kSelThreads) void sel_mask_kernel(SelLaunch S) {
-  __shared__ uint32_t wsum[kSelThreads / 64];
-  const SelState st = *S.state;
-  const int64_t N = live_count(S);
-  const int nt = (int)((N + kSelTile - 1) / kSelTile);
-  // keys above the K-th key: K - rank of them; the remaining `need` come
-  // from the ties at the K-th key, lowest index first
-  const int64_t need = st.rank;
-  for (int t = blockIdx.x; t < nt; t += gridDim.x) {
-    int64_t before = st.k > 0 ? S.tile_offsets[t] : 0;
-    for (int k = 0; k < kSelTile / kSelThreads; ++k) {
-      const int64_t g = (int64_t)t * kSelTile + k * kSelThreads + threadIdx.x;
-      const uint64_t key = g < N ? key_of(S, g) : 0;
-      const bool tie = st.k > 0 && g < N && key == st.kth;
-      uint32_t total = 0;
-      const uint32_t r = sel_scan(tie ? 1u : 0u, wsum, total);
-      if (g < N) S.mask[g] = (uint8_t)(st.k > 0 && (key > st.kth || (tie && before + r < need)));
-      before += total;
+// The rest of the selection, by one work-group. Bound by latency: a list is
+// the candidates of 1/64 of an octave of scores (about 5,000 for 1.2M of 3M
+// Gaussians), 2 passes of 2 us; a list of every candidate (all scores within
+// 1.5%) would take about 0.2 ms a pass for 1.2M entries.
+__global__ __launch_bounds__(kFinThreads) void sel_finish_kernel(SelLaunch S) {
+  __shared__ uint32_t h[kFinBins];
+  __shared__ uint32_t wsum[kFinThreads / 64];
+  __shared__ int64_t pick[3];
+  const int mode = S.state->mode;
+  int64_t need = S.state->need;
+  if (mode == kSelList) {
+    const uint32_t n = S.state->listed;
+    const uint64_t* keys = S.ckeys;
+    const int32_t* rows = S.crows;
+    int shift = open_bits(S.state->bin);
+    uint64_t prefix = n ? keys[0] >> shift : 0;  // the bits that every key of the bin shares
+    uint32_t in = n;
+    while (shift > 0 && need < (int64_t)in) {
+      const int bits = min(shift, kFinBits), s = shift - bits;
+      const uint32_t d = fin_pass<true>(
+          n, [&](uint32_t i) { return (keys[i] >> shift) == prefix; },
+          [&](uint32_t i) { return (uint32_t)(keys[i] >> s) & ((1u << bits) - 1u); }, need, in, h, wsum, pick);
+      prefix = (prefix << bits) | d;
+      shift = s;
     }
+    // `in` entries share the prefix, `need` of them are taken: all, or (equal
+    // keys) those of the lowest rows
+    uint32_t last = 0xFFFFFFFFu;
+    if (need < (int64_t)in) {
+      uint32_t rp = 0;
+      int rs = 33;
+      while (rs > 0) {
+        rs -= kFinBits;
+        const uint32_t d = fin_pass<false>(
+            n, [&](uint32_t i) { return keys[i] == prefix && (rs >= 22 || ((uint32_t)rows[i] >> (rs + kFinBits)) == rp); },
+            [&](uint32_t i) { return ((uint32_t)rows[i] >> rs) & (kFinBins - 1u); }, need, in, h, wsum, pick);
+        rp = (rp << kFinBits) | d;
+      }
+      last = rp;
+    }
+    for (uint32_t i = threadIdx.x; i < n; i += kFinThreads) {
+      const uint64_t q = keys[i] >> shift;
+      if (q > prefix || (q == prefix && (uint32_t)rows[i] <= last)) S.mask[rows[i]] = 1;
+    }
+  } else if (mode == kSelTie) {
+    // the row of the last tie taken: its tile from the counts, then the tile
+    const int64_t N = live_count(S);
+    const int64_t nt = (N + kSelTile - 1) / kSelTile;
+    const int64_t per = (nt + kFinThreads - 1) / kFinThreads, t0 = threadIdx.x * per;
+    uint32_t c = 0;
+    for (int64_t k = 0; k < per; ++k)
+      if (t0 + k < nt) c += S.tile_counts[t0 + k];
+    int64_t before = fin_scan(c, wsum);
+    if (before < need && need <= before + c) {
+      for (int64_t k = 0; k < per; ++k) {
+        const uint32_t tc = t0 + k < nt ? S.tile_counts[t0 + k] : 0;
+        if (need <= before + tc) {
+          pick[0] = t0 + k;
+          pick[1] = need - before;
+          break;
+        }
+        before += tc;
+      }
+    }
+    __syncthreads();
+    const uint64_t key = (uint64_t)S.state->bin;  // a bin below 128 is one exact key
+    const int64_t g0 = pick[0] * kSelTile + 2 * threadIdx.x;
+    const bool a = g0 < N && key_of(S, g0) == key, b = g0 + 1 < N && key_of(S, g0 + 1) == key;
+    const int64_t r = (int64_t)fin_scan((a ? 1u : 0u) + (b ? 1u : 0u), wsum), want = pick[1];
+    if (a && r + 1 == want) S.state->last = g0;
+    if (b && r + (a ? 2 : 1) == want) S.state->last = g0 + 1;
   }
+}
+
+// The tied rows up to the last one taken.
+__global__ __launch_bounds__(kSelThreads) void sel_ties_kernel(SelLaunch S) {
+  if (S.state->mode != kSelTie) return;
+  const int64_t last = S.state->last;
+  const uint64_t key = (uint64_t)S.state->bin;
+  for (int64_t g = (int64_t)blockIdx.x * kSelThreads + threadIdx.x; g <= last; g += (int64_t)gridDim.x * kSelThreads)
+    if (key_of(S, g) == key) S.mask[g] = 1;
 }
 
 }  // namespace
+
+// Shape of the contribution sweep. More rounds of kSelThreads entries per
+// chunk let the LDS table merge more of a Gaussian's image rows, fewer give
+// short lists enough work-groups (2048 fit the chip). Entries beyond half the
+// 256 MB Infinity Cache are read past it (non-temporal), which leaves it to
+// the map lines; smaller lists may still be in it. Whole call, rounds 4 / 8 /
+// 16 / 32: 0.7M entries 28.6 / 30.2 / 35.9 / 50.6 us, 3.5M 46.5 / 44.0 / 45.6
+// / 58.1, 10.5M (non-temporal) 85 / 83 / 89 / 86, 35M 259 / 252 / 245 / 252,
+// 106M 792 / 764 / 739 / 717; plain loads at the best: 3.5M 44.0 (44.5
+// non-temporal), 10.5M 88, 35M 260, 106M 784. A work-group per chunk instead
+// of 2048 sweeping work-groups: 106M 717 -> 696, 10.5M 83 -> 87.
+struct ScatterShape {
+  int rounds;
+  bool nt;
+  int64_t grid;
+};
+
+ScatterShape scatter_shape(int64_t n) {
+  const int64_t m = int64_t(1) << 20;
+  return ScatterShape{n < 2 * m ? 4 : (n < 16 * m ? 8 : (n < 64 * m ? 16 : 32)), n >= 8 * m,
+                      n < 16 * m ? (int64_t)kSelScatterGrid : m};
+}
 
 hipError_t launch_select(const SelLaunch& S, hipStream_t s) {
   const int grid = S.grid;
   hipLaunchKernelGGL(sel_clear_kernel, dim3(grid), dim3(kSelThreads), 0, s, S);
   if (S.n_contrib > 0) {
-    const int64_t chunks = (S.n_contrib + kScatterRounds * kSelThreads - 1) / (kScatterRounds * kSelThreads);
-    const dim3 g((unsigned)(chunks < kSelScatterGrid ? chunks : kSelScatterGrid));
-    if (S.n_views <= kSelLdsViews)
-      hipLaunchKernelGGL(sel_scatter_kernel<true>, g, dim3(kSelThreads), (size_t)S.n_views * sizeof(SelView), s, S);
-    else
-      hipLaunchKernelGGL(sel_scatter_kernel<false>, g, dim3(kSelThreads), 0, s, S);
+    const ScatterShape sh = scatter_shape(S.n_contrib);
+    const int rounds = sh.rounds;
+    const bool nt = sh.nt;
+    const int64_t chunks = (S.n_contrib + rounds * kSelThreads - 1) / (rounds * kSelThreads);
+    const dim3 g((unsigned)(chunks < sh.grid ? chunks : sh.grid)), b(kSelThreads);
+    const bool lds = S.n_views <= kSelLdsViews;
+    const size_t bytes = lds ? (size_t)S.n_views * sizeof(SelView) : 0;
+    if (lds && nt) hipLaunchKernelGGL((sel_scatter_kernel<true, true>), g, b, bytes, s, S, rounds);
+    else if (lds) hipLaunchKernelGGL((sel_scatter_kernel<true, false>), g, b, bytes, s, S, rounds);
+    else if (nt) hipLaunchKernelGGL((sel_scatter_kernel<false, true>), g, b, 0, s, S, rounds);
+    else hipLaunchKernelGGL((sel_scatter_kernel<false, false>), g, b, 0, s, S, rounds);
   }
-  hipLaunchKernelGGL(sel_count_kernel<0>, dim3(grid), dim3(kSelThreads), 0, s, S);
-  hipLaunchKernelGGL(sel_scan_kernel<0>, dim3(1), dim3(1024), 0, s, S);
-  hipLaunchKernelGGL(sel_compact_kernel, dim3(grid), dim3(kSelThreads), 0, s, S);
-  for (int pass = 0; pass < kSelPasses; ++pass)
-    hipLaunchKernelGGL(sel_hist_kernel, dim3(grid), dim3(kSelThreads), 0, s, S, pass);
-  hipLaunchKernelGGL(sel_count_kernel<1>, dim3(grid), dim3(kSelThreads), 0, s, S);
-  hipLaunchKernelGGL(sel_scan_kernel<1>, dim3(1), dim3(1024), 0, s, S);
-  hipLaunchKernelGGL(sel_mask_kernel, dim3(grid), dim3(kSelThreads), 0, s, S);
+  hipLaunchKernelGGL(sel_hist_kernel, dim3(grid < kSelHistGrid ? grid : kSelHistGrid), dim3(kSelThreads), 0, s, S);
+  hipLaunchKernelGGL(sel_collect_kernel, dim3(grid), dim3(kSelThreads), 0, s, S);
+  hipLaunchKernelGGL(sel_finish_kernel, dim3(1), dim3(kFinThreads), 0, s, S);
+  hipLaunchKernelGGL(sel_ties_kernel, dim3(grid), dim3(kSelThreads), 0, s, S);
   return hipGetLastError();
 }
 

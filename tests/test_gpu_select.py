@@ -136,3 +136,26 @@ def test_split_mask_above_one_grid_of_tiles(order, case):
     print(f"{case}/{order}: {c.n} contributions", flush=True)
     K = run(N, N + 777, W, H, c, grad, thr, warm, budget, maps, off)
     assert K == budget - N
+
+
+@pytest.mark.parametrize("N", [4000, 70_001])
+@pytest.mark.parametrize("keys", ["equal", "two", "near_128", "octave"])
+def test_split_mask_bins(N, keys):
+    """The first histogram's bins: every key equal and in one bin with open
+    bits (the ties are taken by row), two values in one bin, exact keys on
+    either side of 128 (bins of one key below, of several above), and keys
+    spread over one octave (64 bins). K falls inside a bin, on its last entry
+    and one past it."""
+    i = np.arange(N)
+    unit = {"equal": np.full(N, 987_654_321), "two": 987_654_321 + 4096 * (i % 2), "near_128": 120 + i % 17,
+            "octave": (1 << 30) + (i * 7919 % N) * ((1 << 30) // N)}[keys]
+    w = (unit * 2.0 ** -32).astype(np.float32)              # E = 1 at the one pixel used
+    W, H, off = [3], [3], np.zeros(1, np.int64)
+    maps = np.ones(9, np.float32)
+    c = synth.Contributions(i.astype(np.int32), np.zeros(N, np.int32), np.full(N, 4, np.int32), w)
+    grad = np.where(i % 5 == 0, 0.1, 1.0).astype(np.float32)    # four fifths are candidates
+    cand = int((grad >= 0.5).sum())
+    scores = oracle.split_scores(maps, W, H, off, c.gauss, c.view, c.pixel, c.weight, N)
+    top = int(((scores == scores.max()) & (grad >= 0.5)).sum())
+    for K in (1, top, top + 1, cand // 2, cand - 1, cand):
+        run(N, N + 3, W, H, c, grad, 0.5, False, N + K, maps, off)
