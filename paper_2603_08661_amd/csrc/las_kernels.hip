@@ -16,7 +16,7 @@
 //               consecutive rows), split_idx[rank] = i. The full-record form
 //               gives the feature copy, each feature moment and the narrow
 //               moments of a tile a work-group of their own.
-// A small plain split (capacity <= 65536 rows) runs the same steps in one
+// A small plain split (capacity <= 16384 rows) runs the same steps in one
 // work-group and one launch (las_small_kernel).
 // All split arithmetic is FP32 in registers; the paper's transform reads
 // only column l of R, computed straight from the normalised quaternion.
@@ -470,10 +470,13 @@ __global__ __launch_bounds__(kLasThreads) __attribute__((amdgpu_waves_per_eu(4))
 // one work-group: it counts the selected rows, takes the capacity decision,
 // then compacts and splits them round by round (8 rows per thread and
 // round). Same rows, same order, same all-or-nothing rule as the three
-// launches; a call then costs one launch instead of three.
+// launches; a call then costs one launch instead of two. The line lies where
+// one work-group's time reaches the other launch's: a call of 10k rows at
+// 10 / 30% takes 12.2 / 14.3 us (16.5 with two launches), 14k 12.2 / 16.6,
+// 20k 16.2 / 22.1, 50k 33.0 / 48.2 (16.5 / 16.7).
 constexpr int kSmallThreads = 1024;
 constexpr int kSmallRows = 8 * kSmallThreads;
-constexpr int64_t kLasSmallCapacity = 8 * kSmallRows;
+constexpr int64_t kLasSmallCapacity = 2 * kSmallRows;
 
 __global__ __launch_bounds__(kSmallThreads) void las_small_kernel(LasLaunch L) {
   __shared__ int32_t rows[kSmallRows];

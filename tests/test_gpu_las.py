@@ -305,3 +305,12 @@ def test_capacity_on_either_side_of_the_folded_scan(tiles, record):
                 assert (after[grp][k] == want).all(), (grp, k)
     else:
         compare(run_las(g, N, mk, cap), N, cap)
+
+
+@pytest.mark.parametrize("cap", [16384, 16385])
+@pytest.mark.parametrize("K", [0, 1, 4000])
+def test_capacity_on_either_side_of_the_one_launch_split(cap, K):
+    """16384 rows are the most the one-launch split takes."""
+    N = cap - K
+    g = synth.gaussians(41, N)
+    compare(run_las(g, N, synth.mask(42, N, K), cap), N, cap)
