@@ -785,57 +785,121 @@ __device__ __forceinline__ void load4(const EdgeLaunch& L, int64_t e, float v[4]
 // persistent kernel, whose register budget is the stencil's and whose four
 // waves per SIMD need more loads each to keep HBM busy.
 constexpr int kWalkUnroll = 4;
+constexpr int kRefineUnroll = 8;  // refinement launches (4: 0.5% slower edge maps)
 constexpr int kPersistWalkUnroll = 12;
+
+constexpr int kLdsCand = 2048;  // candidates a work-group gathers before it flushes them
+
+// The 4 stored values of a lane as raw words (FP32: one each; FP16, BF16: two
+// values a word).
+template <int PREC> struct Raw4 {
+  static constexpr int kWords = PREC == IGSP_FP32 ? 4 : 2;
+  uint32_t w[kWords];
+};
+
+template <int PREC, bool COHERENT>
+__device__ __forceinline__ Raw4<PREC> load_raw4(const EdgeLaunch& L, int64_t e) {
+  Raw4<PREC> r;
+  uint64_t x[PREC == IGSP_FP32 ? 2 : 1];
+  uint64_t* p = PREC == IGSP_FP32 ? reinterpret_cast<uint64_t*>(reinterpret_cast<float*>(L.map) + e)
+                                  : reinterpret_cast<uint64_t*>(reinterpret_cast<uint16_t*>(L.map) + e);
+  if constexpr (COHERENT) {
+#pragma unroll
+    for (int i = 0; i < (int)(sizeof(x) / 8); ++i) x[i] = __hip_atomic_load(p + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  } else if constexpr (PREC == IGSP_FP32) {
+    const u32x4 q = *as_global(reinterpret_cast<const u32x4*>(p));
+    x[0] = q.x | ((uint64_t)q.y << 32);
+    x[1] = q.z | ((uint64_t)q.w << 32);
+  } else {
+    x[0] = *as_global(p);
+  }
+#pragma unroll
+  for (int i = 0; i < Raw4<PREC>::kWords; ++i) r.w[i] = (uint32_t)(x[i >> 1] >> (32 * (i & 1)));
+  return r;
+}
+
+// Which of a lane's 4 values lie in the resolved bucket (bit i: value i), and
+// the next digit of value i. FP32 compares the bits above st.shift; an FP16
+// survivor is a normal number, whose bits above the low three are the
+// widened value's top 16 less (112 << 7), so the halves are compared as they
+// are (widening them first took four times the instructions).
+template <int PREC>
+struct BucketTest {
+  uint32_t key, mask;
+  int shift, dshift;
+  uint32_t prefix, dmask;
+  __device__ __forceinline__ BucketTest(const MedState& st, int digit_bits) {
+    if constexpr (PREC == IGSP_FP16) {
+      const uint32_t h = (st.prefix - (112u << 7)) << 3;
+      key = h | (h << 16);
+      mask = 0xFFF8FFF8u;
+    }
+    shift = st.shift;
+    dshift = st.shift - digit_bits;
+    prefix = st.prefix;
+    dmask = (1u << digit_bits) - 1u;
+  }
+  __device__ __forceinline__ uint32_t hits(const Raw4<PREC>& r) const {
+    uint32_t m = 0;
+    if constexpr (PREC == IGSP_FP16) {
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        const uint32_t t = (r.w[k] ^ key) & mask;
+        m |= (t & 0xFFFFu) == 0u ? 1u << (2 * k) : 0u;
+        m |= t < 0x10000u ? 2u << (2 * k) : 0u;
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) m |= (r.w[i] >> shift) == prefix ? 1u << i : 0u;
+    }
+    return m;
+  }
+  __device__ __forceinline__ uint32_t digit(const Raw4<PREC>& r, int i) const {
+    if constexpr (PREC == IGSP_FP16) return (r.w[i >> 1] >> (16 * (i & 1))) & 7u;
+    else return (r.w[i] >> dshift) & dmask;
+  }
+};
 
 // Digit histogram (into LDS) of a chunk's survivors inside the resolved
 // bucket of the radix selection, by the NW wavefronts of a work-group.
 // APPEND also gathers each of them in the work-group's LDS list lds_cand
 // (count in *lds_n; the first FP32 pass: the second then reads the view's
-// list instead of the map).
-constexpr int kLdsCand = 2048;  // candidates a work-group gathers before it flushes them
-
+// list instead of the map). A bucket's prefix is never that of 0, so values
+// that did not survive are never inside it.
 template <int PREC, int NW, bool COHERENT, bool APPEND = false>
 __device__ __forceinline__ void refine_slots(const EdgeLaunch& L, const ViewDesc& vd, const RowChunk& ck,
                                              const MedState& st, int digit_bits, uint32_t* hs, int lane, int wave,
                                              uint32_t* lds_cand = nullptr, uint32_t* lds_n = nullptr) {
-  constexpr int kRefineUnroll = COHERENT ? kPersistWalkUnroll : kWalkUnroll;
+  constexpr int U = COHERENT ? kPersistWalkUnroll : kRefineUnroll;
   const int ns = strips_of(vd);
-  const int dshift = st.shift - digit_bits;
-  const uint32_t dmask = (1u << digit_bits) - 1u;
-  // kRefineUnroll slots' loads in flight per wavefront (slots past the
+  const BucketTest<PREC> test(st, digit_bits);
+  // U slots' loads in flight per wavefront (slots past the
   // chunk's end load the last slot again and count nothing)
-  for (int u0 = ck.u0 + wave; u0 < ck.u1; u0 += kRefineUnroll * NW) {
-    SlotAt a[kRefineUnroll];
-    float v[kRefineUnroll][4];
+  for (int u0 = ck.u0 + wave; u0 < ck.u1; u0 += U * NW) {
+    int valid[U];
+    Raw4<PREC> v[U];
 #pragma unroll
-    for (int k = 0; k < kRefineUnroll; ++k) {
-      a[k] = view_slot(vd, ns, min(u0 + k * NW, ck.u1 - 1), lane);
-      load4<PREC, COHERENT>(L, a[k].stored, v[k]);
+    for (int k = 0; k < U; ++k) {
+      const SlotAt a = view_slot(vd, ns, min(u0 + k * NW, ck.u1 - 1), lane);
+      valid[k] = a.valid;
+      v[k] = load_raw4<PREC, COHERENT>(L, a.stored);
     }
-    uint32_t hit = 0;  // bit 4k + i: value i of slot k is counted
 #pragma unroll
-    for (int k = 0; k < kRefineUnroll; ++k) {
+    for (int k = 0; k < U; ++k) {
       if (u0 + k * NW >= ck.u1) break;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const uint32_t bits = __float_as_uint(v[k][i]);
-        if (i < a[k].valid && v[k][i] > 0.0f && (bits >> st.shift) == st.prefix) {
-          atomicAdd(&hs[(bits >> dshift) & dmask], 1u);
-          hit |= 1u << (4 * k + i);
-        }
-      }
-    }
-    if constexpr (APPEND) {
-      // the counted values go to the work-group's LDS list (flushed to the
-      // view's list once per work-group by the caller)
-#pragma unroll
-      for (int k = 0; k < kRefineUnroll; ++k)
+      uint32_t m = test.hits(v[k]);
+      m = valid[k] >= kLanePx ? m : (valid[k] > 0 ? m & ((1u << valid[k]) - 1u) : 0u);
+      if (m) {  // a few in a thousand pixels
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-          if ((hit >> (4 * k + i)) & 1u) {
-            const uint32_t at = atomicAdd(lds_n, 1u);
-            if (at < (uint32_t)kLdsCand) lds_cand[at] = __float_as_uint(v[k][i]);
+          if ((m >> i) & 1u) {
+            atomicAdd(&hs[test.digit(v[k], i)], 1u);
+            if constexpr (APPEND) {
+              const uint32_t at = atomicAdd(lds_n, 1u);
+              if (at < (uint32_t)kLdsCand) lds_cand[at] = v[k].w[i];
+            }
           }
+      }
     }
   }
 }
@@ -851,7 +915,13 @@ __global__ __launch_bounds__(256) void median_refine_kernel(EdgeLaunch L, int ch
   __shared__ uint32_t tmp[4];
   __shared__ MedState s_st;
   constexpr int DB = refine_digit_bits(PREC);
-  const RowChunk ck = L.chunks[chunk0 + blockIdx.x];
+  // FP32's 4-byte map: the stencil's last writes first (each XCD's share of
+  // the list from its end), while they are still in the Infinity Cache: 24
+  // views (48 MPx) 229 -> 219 us of edge maps, 150 views 669 -> 662. FP16's
+  // 2-byte map gained nothing (642 -> 643 us, 200 views), nor did reversing the
+  // normalisation.
+  const int at = PREC == IGSP_FP32 ? (int)gridDim.x - 1 - xcd_remap((int)blockIdx.x, (int)gridDim.x) : (int)blockIdx.x;
+  const RowChunk ck = L.chunks[chunk0 + at];
   const int v = ck.view;
   const int64_t n = L.n_views;
   MedState st = L.state[v];
@@ -888,8 +958,8 @@ __global__ __launch_bounds__(256) void median_refine_kernel(EdgeLaunch L, int ch
       // map: every survivor of the new bucket is one of them. The view's
       // chunks share the list evenly, in chunk order.
       const uint32_t nc = L.cand_n[v];
-      const uint32_t chunks = (uint32_t)((strips_of(vd) * (int64_t)vd.H + kRefineChunkSlots - 1) / kRefineChunkSlots);
-      const uint32_t j = (uint32_t)(ck.u0 / kRefineChunkSlots), per = (nc + chunks - 1) / chunks;
+      const uint32_t chunks = (uint32_t)((strips_of(vd) * (int64_t)vd.H + L.refine_slots - 1) / L.refine_slots);
+      const uint32_t j = (uint32_t)(ck.u0 / L.refine_slots), per = (nc + chunks - 1) / chunks;
       const uint32_t c0 = min(nc, j * per), c1 = min(nc, c0 + per);
       const int dshift = st.shift - DB;
       for (uint32_t k = c0 + threadIdx.x; k < c1; k += 256) {

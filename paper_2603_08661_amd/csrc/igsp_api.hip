@@ -84,6 +84,8 @@ struct EdgePlan {
   EdgeItem* d_items_all = nullptr;  // the same items in the order of a launch over every view
   RowChunk* d_chunks = nullptr;
   RowChunk* d_rchunks = nullptr;  // the refinement passes' coarser chunks
+  RowChunk* d_wide = nullptr;     // FP32: coarser still, for launches over every view (n_wide = 0: not used)
+  int n_wide = 0;
   uint32_t* d_cand = nullptr;     // FP32: median candidates and their counts per view
   uint32_t* d_cand_n = nullptr;
   std::vector<int> item_begin, chunk_begin, rchunk_begin;  // per view, size n_views + 1
@@ -103,7 +105,7 @@ struct EdgePlan {
   int64_t map_elems = 0;
   ~EdgePlan() {
     (void)hipFree(d_views); (void)hipFree(d_items); (void)hipFree(d_items_all); (void)hipFree(d_chunks);
-    (void)hipFree(d_rchunks); (void)hipFree(d_cand); (void)hipFree(d_cand_n); (void)hipFree(d_map);
+    (void)hipFree(d_rchunks); (void)hipFree(d_wide); (void)hipFree(d_cand); (void)hipFree(d_cand_n); (void)hipFree(d_map);
     (void)hipFree(d_hist); (void)hipFree(d_rhist); (void)hipFree(d_state);
     (void)hipFree(d_pchunks); (void)hipFree(d_tasks); (void)hipFree(d_sync); (void)hipFree(d_ctl);
     (void)hipFree(const_cast<UfItem*>(uf.items)); (void)hipFree(uf.gray); (void)hipFree(uf.blur);
@@ -289,7 +291,7 @@ igsp_status build_edge_plan(const EdgeKey& key, std::shared_ptr<EdgePlan>* out) 
   const int esz = key.precision == IGSP_FP32 ? 4 : 2;
   std::vector<ViewDesc> vd(n);
   std::vector<EdgeItem> items;
-  std::vector<RowChunk> chunks, rchunks;
+  std::vector<RowChunk> chunks, rchunks, wide;
   plan->item_begin.resize(n + 1);
   plan->chunk_begin.resize(n + 1);
   plan->rchunk_begin.resize(n + 1);
@@ -317,11 +319,14 @@ igsp_status build_edge_plan(const EdgeKey& key, std::shared_ptr<EdgePlan>* out) 
     row_chunks(v, d.width, d.height, kChunkSlots, &chunks);
     plan->rchunk_begin[v] = (int)rchunks.size();
     row_chunks(v, d.width, d.height, kRefineChunkSlots, &rchunks);
+    row_chunks(v, d.width, d.height, kRefineWideSlots, &wide);
   }
   plan->item_begin[n] = (int)items.size();
   plan->chunk_begin[n] = (int)chunks.size();
   plan->rchunk_begin[n] = (int)rchunks.size();
   plan->map_elems = map_elems;
+  if (key.precision != IGSP_FP32 || n < 2 || map_elems / kSlotPitch < kWideSlots) wide.clear();
+  plan->n_wide = (int)wide.size();
   // A launch over every view gives each XCD a contiguous eighth of the list
   // (the kernel's block remap); inside each eighth, full bands come first and
   // the shorter last bands of the strips after them, longest first, so the
@@ -338,7 +343,8 @@ igsp_status build_edge_plan(const EdgeKey& key, std::shared_ptr<EdgePlan>* out) 
   }
   if (upload(&plan->d_views, vd) != hipSuccess || upload(&plan->d_items, items) != hipSuccess ||
       upload(&plan->d_items_all, all) != hipSuccess ||
-      upload(&plan->d_chunks, chunks) != hipSuccess || upload(&plan->d_rchunks, rchunks) != hipSuccess)
+      upload(&plan->d_chunks, chunks) != hipSuccess || upload(&plan->d_rchunks, rchunks) != hipSuccess ||
+      upload(&plan->d_wide, wide) != hipSuccess)
     return IGSP_ERR_HIP;
   if (hipMalloc(&plan->d_map, (size_t)std::max<int64_t>(map_elems, 64) * esz) != hipSuccess) return IGSP_ERR_HIP;
   if (cand_elems > 0 &&
@@ -535,6 +541,7 @@ igsp_status enqueue_edge(EdgePlan* P, const uint8_t* images, int64_t img_end, fl
   L.cand = P->d_cand;
   L.cand_n = P->d_cand_n;
   L.use_cand = 0;
+  L.refine_slots = kRefineChunkSlots;
   L.short_chain = 0;
   L.n_views = P->n_views;
   L.medians_dn = opts ? opts->medians : nullptr;
@@ -557,9 +564,11 @@ igsp_status enqueue_edge(EdgePlan* P, const uint8_t* images, int64_t img_end, fl
   // selection step is taken by the normalisation
   auto tail = [&](int v0, int v1, hipStream_t st) -> hipError_t {
     if (is_short(v0, v1)) return launch_median_gather(L, P->chunk_begin[v0], P->chunk_begin[v1] - P->chunk_begin[v0], st);
-    const int f0 = P->rchunk_begin[v0], f1 = P->rchunk_begin[v1];
+    const bool wide = P->n_wide > 0 && v0 == 0 && v1 == n;
+    const int f0 = wide ? 0 : P->rchunk_begin[v0], f1 = wide ? P->n_wide : P->rchunk_begin[v1];
     EdgeLaunch LR = L;
-    LR.chunks = P->d_rchunks;
+    LR.chunks = wide ? P->d_wide : P->d_rchunks;
+    LR.refine_slots = wide ? kRefineWideSlots : kRefineChunkSlots;
     // FP32 candidate lists where a launch covers several views (one view's
     // launches are bound by latency, and the list's extra steps cost more
     // than the second pass's bytes: +2% for the plain form, measured)

@@ -38,7 +38,14 @@ constexpr uint32_t kKeyLoSquare = 127u * 128u;             // float32 exponent o
 constexpr int kBinsSquare = 58 * 128;                      // 1 .. 2^58
 constexpr int kBinsMax = kBinsSquare;
 constexpr int kRefineBins = 256;          // radix digit of the refine passes
-constexpr int kRefineChunkSlots = 64;     // slots per work-group of a refinement pass
+// Slots per work-group of a refinement pass (each clears and flushes a
+// histogram), and of FP32's passes over at least kWideSlots slots of several
+// views. 32 / 64 / 128 slots: 24 FP32 views (48 MPx) 237 / 214 / 209 us of edge
+// maps, 200 FP16 views 637 / 639 / 645; one FP32 view of 3.7 MPx 64 / 128:
+// 49.8 / 54.2 (too few work-groups), 8 MPx 63.3 / 62.6, 15 MPx 88.4 / 83.6.
+constexpr int kRefineChunkSlots = 64;
+constexpr int kRefineWideSlots = 128;
+constexpr int64_t kWideSlots = 40000;
 // Slots (248 pixels each) per work-group of the other element-wise passes,
 // about 4 Ki pixels (measured best for normalisation).
 constexpr int kChunkSlots = 16;
@@ -103,6 +110,7 @@ struct EdgeLaunch {
   uint32_t* cand;            // FP32: survivors in the first histogram's median bucket, per view (short chain:
                              // pairs of value and count)
   uint32_t* cand_n;          // [n_views]: candidates found (more than the room: list not used)
+  int refine_slots;          // slots per chunk of this refinement launch
   int use_cand;              // the refinement passes of this launch use the candidate lists
   int short_chain;           // the median takes one launch (median_gather) before the normalisation
   float* medians_dn;         // optional outputs

@@ -260,3 +260,18 @@ def test_short_and_long_median_chain(precision, rows):
     a, ma, na = gpu_edge(vb, precision, "staged", reps=2)
     b, mb, nb = gpu_edge(vb, precision, "unfused")
     assert np.array_equal(a, b) and np.array_equal(ma, mb) and np.array_equal(na, nb) and na[0] > 0
+
+
+@pytest.mark.parametrize("rows", [2500, 2499])
+def test_fp32_wide_refinement_chunks(rows):
+    """Two views of 8 strips x 2500 rows are 40000 slots, the fewest whose FP32
+    refinement takes 128 slots per work-group; one row less takes 64. One view
+    is textured (its second pass reads the candidate list), one striped (the
+    list overflows, the pass reads the map). Both equal the persistent form
+    bit for bit."""
+    stripes = np.zeros((rows, 1984, 3), np.uint8)
+    stripes[:] = ((((np.arange(1984) // 3) % 2) * 180) + 30).astype(np.uint8)[None, :, None]
+    vb = synth.pack_views([synth.image(62, 1984, rows, n_poly=20, texture=True), stripes], in_align=16, out_align=4)
+    a, ma, na = gpu_edge(vb, "fp32", "staged", reps=2)
+    b, mb, nb = gpu_edge(vb, "fp32", "persistent")
+    assert np.array_equal(a, b) and np.array_equal(ma, mb) and np.array_equal(na, nb) and (na > 0).all()
