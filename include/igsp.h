@@ -108,9 +108,10 @@ typedef enum {
 typedef struct {
   int32_t precision;     /* igsp_precision                                    */
   int32_t batched;       /* igsp_form                                         */
-  int32_t seg_rows;      /* output rows per wavefront segment; 0 = tuned (at
-                            the shortest, 10, views too few to fill the chip
-                            are marched in shorter segments still)            */
+  int32_t seg_rows;      /* output rows per wavefront segment; 0 = tuned.
+                            Marched in whole rounds of six rows, and at 10
+                            rows in single rounds where the views are too
+                            few to fill the chip                              */
   int32_t wg_waves;      /* wavefronts per work-group (1, 2, 4, 8); 0 = tuned */
   float* medians;        /* (device, optional) [n_views]: the median surviving
                             magnitude of each view, in DN per pixel of an

@@ -135,8 +135,7 @@ int device_cus() {
 // else the shortest. A wavefront's march is a chain of dependent rows, so a
 // launch with fewer wavefronts than the chip holds lasts about one segment:
 // shorter segments then save more time than their extra halo rows cost. The
-// plain form launches each view on its own, so it counts per view. (Each
-// height plus the 8 halo rows is a multiple of the loop's 6-row unroll.)
+// plain form launches each view on its own, so it counts per view.
 constexpr int kShortestSeg = 10;
 
 // Wavefronts of a stencil launch over the views at a segment height.
@@ -158,18 +157,21 @@ int default_seg_rows(const igsp_view* views, int32_t n, int form) {
   return kShortestSeg;
 }
 
-// A plan of the shortest segments whose wavefronts would leave most SIMDs
-// idle splits them once more, to 4 rows (12 with the halo, two rounds of the
-// unroll): a lone wavefront takes 0.48 us a row, and six rows fewer save more
-// than the extra halo rows and histogram flushes cost while no two wavefronts
-// share a SIMD. One FP32 256x192 view (96 wavefronts at 4 rows): 25.1 -> 22.0
-// us; 1297x840 (1260): 32.0 -> 32.8; 40 ragged views (FP16, 1300): 34.0 ->
-// 36.5, so the line is at two wavefronts per CU.
-constexpr int kSplitSeg = 4;
+// Rows per segment as a plan marches them: whole rounds of the stencil loop's
+// six rows (the rows past a segment's end would be computed all the same;
+// 150 views BF16, 100 rows marched as 102: 864 -> 855 us of edge maps). A plan
+// of the shortest segments whose wavefronts would leave most SIMDs with one
+// or none splits them once more, to one round: a lone wavefront takes about
+// 0.5 us a row, and shorter segments save more than their window-filling rows
+// (2.7 rows' work) and histogram flushes cost. At 10 rows marched as 12 / 6:
+// one FP32 256x192 view (64 wavefronts at 6 rows) 22.8 / 19.9 us, 1297x840
+// (840) 29.4 / 28.1, 1600x1067 (1246) 34.7 / 34.4, two 1297x840 (1680) 37.4 /
+// 37.6: the line is at 1.5 wavefronts per SIMD.
+constexpr int kRound = 6;
 
 int plan_seg_rows(const igsp_view* views, int32_t n, int seg) {
-  if (seg == kShortestSeg && stencil_waves(views, n, kSplitSeg) <= 2 * (int64_t)device_cus()) return kSplitSeg;
-  return seg;
+  if (seg == kShortestSeg && stencil_waves(views, n, kRound) <= 6 * (int64_t)device_cus()) return kRound;
+  return (seg + kRound - 1) / kRound * kRound;
 }
 
 // ------------------------------------------------------------------ tuning
@@ -944,8 +946,7 @@ extern "C" igsp_status igsp_edge_autotune(const uint8_t* images, const igsp_view
   if (st != IGSP_OK) return st;
   if (n_views == 0) return IGSP_OK;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  // segment heights whose rows plus the 8 halo rows are a multiple of the
-  // stencil loop's 6-row unroll (no row computed past a full segment's end)
+  // segment heights (each marched in whole rounds of six rows)
   static const int kSeg[] = {10, 16, 22, 28, 40, 64, 88, 100, 124, 148, 196, 244};
   static const int kWaves[] = {1, 2, 4, 8};
   std::vector<int> forms;

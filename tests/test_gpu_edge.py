@@ -275,3 +275,25 @@ def test_fp32_wide_refinement_chunks(rows):
     a, ma, na = gpu_edge(vb, "fp32", "staged", reps=2)
     b, mb, nb = gpu_edge(vb, "fp32", "persistent")
     assert np.array_equal(a, b) and np.array_equal(ma, mb) and np.array_equal(na, nb) and (na > 0).all()
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp16", "bf16"])
+@pytest.mark.parametrize("seg_rows", [0, 8, 13, 64])
+def test_ties_and_segment_remainders(precision, seg_rows):
+    """Flat blocks, steps and stripes make magnitudes that equal a neighbour's
+    (the tie rule decides, on a path of its own); heights from one to two
+    rounds of the stencil's six rows past the segment give every remainder.
+    All equal the unfused form, which always applies the whole rule."""
+    rng = np.random.default_rng(31)
+    imgs = []
+    for h in range(64, 78):
+        blocks = np.kron(rng.integers(0, 4, (h // 8 + 1, 40, 3)) * 60, np.ones((8, 7, 1), int))[:h, :270]
+        imgs.append(blocks.astype(np.uint8))
+    imgs += [np.ascontiguousarray(im.transpose(1, 0, 2)) for im in imgs[:3]]
+    vb = synth.pack_views(imgs, in_align=1, out_align=3)
+    a, ma, na = gpu_edge(vb, precision, "staged", seg_rows=seg_rows, reps=2)
+    b, mb, nb = gpu_edge(vb, precision, "unfused")
+    for v in range(vb.n):
+        assert np.array_equal(view_map(a, vb, v), view_map(b, vb, v)), v
+    assert np.array_equal(ma, mb) and np.array_equal(na, nb) and (na > 0).all()
+    check_batch(vb, precision, "plain", views=[0, 13, 16])
