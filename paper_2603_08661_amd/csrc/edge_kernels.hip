@@ -221,10 +221,13 @@ __device__ __forceinline__ Lane12 load_lane_bytes(__amdgpu_buffer_rsrc_t row, co
 // BT.601 luma x 1000 of 4 packed pixels (12 bytes in d0..d2) with byte dot
 // products: 299 = 256 + 43, 587 = 2*256 + 75, 114 = 114.
 __device__ __forceinline__ void gray4(uint32_t d0, uint32_t d1, uint32_t d2, int g[4]) {
+  // the middle pixels' bytes moved into words of their own (an alignment and
+  // two products each; straddling words took four and three products)
+  const uint32_t p1 = __builtin_amdgcn_alignbyte(d1, d0, 3);                               // R1 G1 B1 -
   const uint32_t lo0 = __builtin_amdgcn_udot4(d0, 0x00724B2Bu, 0u, false);               // R0 G0 B0
   const uint32_t hi0 = __builtin_amdgcn_udot4(d0, 0x00000201u, 0u, false);
-  const uint32_t lo1 = __builtin_amdgcn_udot4(d1, 0x0000724Bu, __builtin_amdgcn_udot4(d0, 0x2B000000u, 0u, false), false);
-  const uint32_t hi1 = __builtin_amdgcn_udot4(d1, 0x00000002u, __builtin_amdgcn_udot4(d0, 0x01000000u, 0u, false), false);
+  const uint32_t lo1 = __builtin_amdgcn_udot4(p1, 0x00724B2Bu, 0u, false);
+  const uint32_t hi1 = __builtin_amdgcn_udot4(p1, 0x00000201u, 0u, false);
   const uint32_t lo2 = __builtin_amdgcn_udot4(d2, 0x00000072u, __builtin_amdgcn_udot4(d1, 0x4B2B0000u, 0u, false), false);
   const uint32_t hi2 = __builtin_amdgcn_udot4(d1, 0x02010000u, 0u, false);
   const uint32_t lo3 = __builtin_amdgcn_udot4(d2, 0x724B2B00u, 0u, false);               // R3 G3 B3
@@ -348,8 +351,8 @@ template <bool NARROW>
 constexpr int kRowsHeld = NARROW ? 2 : 6;
 
 // How much of a row's work its step does: the first steps of a march only
-// fill the windows (8.75, 14.25 and 21.75 vector operations a pixel against
-// 39.25 for a whole step).
+// fill the windows (8.5, 14 and 21.5 vector operations a pixel against 39 for
+// a whole step, BF16).
 enum Stage {
   kStageBlurX = 0,  // steps 0-3: grayscale, horizontal blur and its pair sums
   kStageBlur = 1,   // steps 4-5: also the vertical blur and its differences
@@ -647,7 +650,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(IGSP_FU
   // the short chain's counts start from zero (the long chain's selection
   // launch clears them itself)
   if (L.short_chain && it.x0 == 0 && it.y0 == 0) {
-    if (threadIdx.x < 8) L.rhist[(int64_t)it.view * kRefineBins + threadIdx.x] = 0;
+    for (int i = threadIdx.x; i < kRefineBins; i += NW * 64) L.rhist[(int64_t)it.view * kRefineBins + i] = 0;
     if (L.cand_n && threadIdx.x == 0) L.cand_n[it.view] = 0;
   }
   __syncthreads();
@@ -1082,12 +1085,17 @@ __device__ __forceinline__ MedState refine_step8(const MedState& st, cptr<uint32
 // its size, so the median takes one launch between the stencil and the
 // normalisation instead of three. median_gather selects the median's bucket
 // from the first histogram in every work-group (29 KB from L2) and counts
-// (FP16) or lists (FP32) the survivors inside it; the normalisation's
+// (FP16) or lists and counts (FP32) the survivors inside it; the normalisation's
 // work-groups finish the selection from those, and its first chunk of a view
 // clears the histogram. A 256x192 FP32 view's edge maps: 35.9 us with five
-// launches, 25.0 with these three (22.0 with its segments split as well);
-// 1297x840: 40.7 and 32.0. Latency-bound: the stencil's lone wavefronts take
-// 13.5-18 us, the other two launches 5-8 us each.
+// launches, 25.0 with these three (19.7 with its segments split and their
+// first rows made cheap); 1297x840: 40.7 and 32.0 (27.5). Latency-bound: the
+// stencil's lone wavefronts take 9-13 us, the other two launches 5-8 us each.
+// FP32's first digit counted by median_gather (a few hundred global atomics)
+// saves the normalisation a pass over the list: 1297x840 28.4 -> 27.5. Sums of
+// the histogram over whole binades, for median_gather to read instead of its
+// 7424 bins, cost the stencil more than they saved: every work-group adds to
+// the same few words, about 100 ns an addition (1297x840: 28.4 -> 69.4 us).
 
 // The state after the first histogram, taken by a whole work-group (bins: its
 // LDS copy; each thread sums PER consecutive bins, an odd number, so the reads
@@ -1182,7 +1190,10 @@ __global__ __launch_bounds__(256) void median_gather_kernel(EdgeLaunch L, int ch
       const uint32_t bits = __float_as_uint(q[k][i]);
       if (i < a[k].valid && (bits >> 16) == st.prefix) {
         if constexpr (PREC == IGSP_FP16) atomicAdd(&lds[(bits >> 13) & 7u], 1u);
-        else lds[atomicAdd(&cn, 1u)] = bits;
+        else {
+          lds[atomicAdd(&cn, 1u)] = bits;
+          atomicAdd(&L.rhist[(int64_t)v * kRefineBins + ((bits >> 8) & 255u)], 1u);
+        }
       }
     }
   }
@@ -1223,31 +1234,28 @@ __global__ __launch_bounds__(256) void median_gather_kernel(EdgeLaunch L, int ch
 }
 
 // The rest of FP32's selection (16 bits, two digits of 8) by one work-group:
-// from the view's candidate list, or from the stored map where the list had
-// no room (hs: 256 words of LDS).
+// the first digit from median_gather's counts, the second from the view's
+// candidate list, or from the stored map where the list had no room (hs: 256
+// words of LDS).
 __device__ __forceinline__ MedState resolve_view(const EdgeLaunch& L, int v, const ViewDesc& vd, MedState st, uint32_t* hs,
                                                  uint32_t* tmp, MedState* s_st) {
   if (st.n == 0) return st;
   const uint32_t nc = L.cand_n[v];
   const uint2* list = reinterpret_cast<const uint2*>(L.cand) + vd.cand_off;
-  for (int pass = 0; pass < 2; ++pass) {
-    hs[threadIdx.x] = 0;
-    __syncthreads();
-    const int dshift = st.shift - 8;
-    if (nc <= (uint32_t)vd.cand_cap) {
-      for (uint32_t k = threadIdx.x; k < nc; k += 256) {
-        const uint2 e = list[k];
-        if ((e.x >> st.shift) == st.prefix) atomicAdd(&hs[(e.x >> dshift) & 255u], e.y);
-      }
-    } else {
-      const RowChunk all = {v, 0, strips_of(vd) * vd.H, 0};
-      refine_slots<IGSP_FP32, 4, false>(L, vd, all, st, 8, hs, __lane_id(),
-                                        __builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
+  hs[threadIdx.x] = 0;
+  st = refine_step(L, st, L.rhist + (int64_t)v * kRefineBins, 8, tmp, s_st);
+  if (nc <= (uint32_t)vd.cand_cap) {
+    for (uint32_t k = threadIdx.x; k < nc; k += 256) {
+      const uint2 e = list[k];
+      if ((e.x >> 8) == st.prefix) atomicAdd(&hs[e.x & 255u], e.y);
     }
-    __syncthreads();
-    st = refine_step(L, st, hs, 8, tmp, s_st);
+  } else {
+    const RowChunk all = {v, 0, strips_of(vd) * vd.H, 0};
+    refine_slots<IGSP_FP32, 4, false>(L, vd, all, st, 8, hs, __lane_id(),
+                                      __builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
   }
-  return st;
+  __syncthreads();
+  return refine_step(L, st, hs, 8, tmp, s_st);
 }
 
 // ------------------------------------------------------------- stage 3
