@@ -638,6 +638,18 @@ __device__ __forceinline__ void wave_strip(const EdgeLaunch& L, const ViewDesc& 
   else march<PREC, false, CPOL>(C, hist);
 }
 
+// This item's share of clearing its view's counts of the short chain, an equal
+// part for each of the view's items.
+__device__ __forceinline__ void clear_fine_share(const EdgeLaunch& L, const ViewDesc& vd, const EdgeItem& it, int band,
+                                                 int threads) {
+  constexpr int64_t kWords = kFineBins / 4;
+  const int bands = (vd.H + band - 1) / band, items = ((vd.W + kStripCols - 1) / kStripCols) * bands;
+  const int i = it.x0 / kStripCols * bands + it.y0 / band;
+  u32x4* f = reinterpret_cast<u32x4*>(L.fine + (int64_t)(it.view - L.view0) * kFineBins);
+  const int end = (int)(kWords * (i + 1) / items);
+  for (int k = (int)(kWords * i / items) + (int)threadIdx.x; k < end; k += threads) f[k] = u32x4{0u, 0u, 0u, 0u};
+}
+
 template <int PREC, int NW>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(IGSP_FUSED_WAVES_PER_EU))) void edge_fused_kernel(EdgeLaunch L, int item0, int n_items) {
   constexpr int NB = Keys<PREC>::bins;
@@ -651,7 +663,9 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(IGSP_FU
   // launch clears them itself)
   if (L.short_chain && it.x0 == 0 && it.y0 == 0) {
     for (int i = threadIdx.x; i < kRefineBins; i += NW * 64) L.rhist[(int64_t)it.view * kRefineBins + i] = 0;
-    if (L.cand_n && threadIdx.x == 0) L.cand_n[it.view] = 0;
+  }
+  if constexpr (PREC == IGSP_FP32) {
+    if (L.short_chain) clear_fine_share(L, vd, it, L.seg_rows * NW, NW * 64);
   }
   __syncthreads();
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1085,14 +1099,13 @@ __device__ __forceinline__ MedState refine_step8(const MedState& st, cptr<uint32
 // its size, so the median takes one launch between the stencil and the
 // normalisation instead of three. median_gather selects the median's bucket
 // from the first histogram in every work-group (29 KB from L2) and counts
-// (FP16) or lists and counts (FP32) the survivors inside it; the normalisation's
-// work-groups finish the selection from those, and its first chunk of a view
+// the survivors inside it by the bits that it leaves open; the normalisation's
+// work-groups finish the selection from those counts, and its first chunk of a view
 // clears the histogram. A 256x192 FP32 view's edge maps: 35.9 us with five
 // launches, 25.0 with these three (19.7 with its segments split and their
 // first rows made cheap); 1297x840: 40.7 and 32.0 (27.5). Latency-bound: the
 // stencil's lone wavefronts take 9-13 us, the other two launches 5-8 us each.
-// FP32's first digit counted by median_gather (a few hundred global atomics)
-// saves the normalisation a pass over the list: 1297x840 28.4 -> 27.5. Sums of
+// Sums of
 // the histogram over whole binades, for median_gather to read instead of its
 // 7424 bins, cost the stencil more than they saved: every work-group adds to
 // the same few words, about 100 ns an addition (1297x840: 28.4 -> 69.4 us).
@@ -1137,27 +1150,25 @@ __device__ __forceinline__ MedState select_first(const EdgeLaunch& L, int v, uin
   return *s_st;
 }
 
-// An entry of a view's candidate list: a stored value and how often it occurs.
-__device__ __forceinline__ void add_candidate(const EdgeLaunch& L, const ViewDesc& vd, int v, uint32_t at, uint32_t bits,
-                                              uint32_t n) {
-  if (at < (uint32_t)vd.cand_cap) reinterpret_cast<uint2*>(L.cand)[vd.cand_off + at] = make_uint2(bits, n);
-}
-
-// LDS of median_gather, in words: the first histogram, then (once it has been
-// used) the chunk's candidates and a table of distinct values.
-constexpr int kGatherList = kChunkSlots * kStripCols;  // a chunk's pixels
-constexpr int kGatherTable = 1024;                     // values, then their counts
-static_assert(kGatherList + 2 * kGatherTable <= kBinsMax, "fits the histogram's LDS");
-// A work-group with more candidates than this lists distinct values with
-// their counts (flat graphics put most survivors on a few magnitudes).
-constexpr uint32_t kGatherPlain = 256;
+// FP32's open 16 bits are counted exactly: kFineBins counts a view (256 KiB,
+// cleared by the stencil's work-groups), and their sums over the upper 8 bits
+// in rhist. Every work-group first merges its equal values, since additions to
+// one address follow one another at about 11 ns: without that, 6-pixel stripes
+// of one magnitude took 4.1 ms at 1297x840. Up to kGatherFew candidates are
+// merged by one wavefront, lane against lane; more by an LDS table with room
+// for every pixel of the chunk (the low 16 bits and their count in one word;
+// a count is at least 1, so a free word is 0).
+constexpr uint32_t kGatherFew = 64;
+constexpr int kGatherTable = 4096;
+static_assert(kChunkSlots * kStripCols < kGatherTable, "the table never fills");
+static_assert(kRefineBins + kGatherTable <= kBinsMax, "fits the histogram's LDS");
 
 template <int PREC>
 __global__ __launch_bounds__(256) void median_gather_kernel(EdgeLaunch L, int chunk0) {
   __shared__ __attribute__((aligned(16))) uint32_t lds[kBinsMax];
   __shared__ uint32_t tmp[4];
   __shared__ MedState s_st;
-  __shared__ uint32_t cn, cbase;
+  __shared__ uint32_t cn;
   const RowChunk ck = L.chunks[chunk0 + blockIdx.x];
   const int v = ck.view;
   const ViewDesc vd = L.views[v];
@@ -1179,83 +1190,94 @@ __global__ __launch_bounds__(256) void median_gather_kernel(EdgeLaunch L, int ch
     if (ck.u0 == 0) L.state[v] = st;
   }
   if (st.n == 0) return;  // uniform: no survivor
-  if (threadIdx.x < 8) lds[threadIdx.x] = 0;
-  if (threadIdx.x == 0) cn = 0;
-  __syncthreads();
+  if constexpr (PREC == IGSP_FP16) {
+    if (threadIdx.x < 8) lds[threadIdx.x] = 0;
+    __syncthreads();
 #pragma unroll
-  for (int k = 0; k < kWalkUnroll; ++k) {
-    if (ck.u0 + wave + 4 * k >= ck.u1) break;
+    for (int k = 0; k < kWalkUnroll; ++k) {
+      if (ck.u0 + wave + 4 * k >= ck.u1) break;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const uint32_t bits = __float_as_uint(q[k][i]);
-      if (i < a[k].valid && (bits >> 16) == st.prefix) {
-        if constexpr (PREC == IGSP_FP16) atomicAdd(&lds[(bits >> 13) & 7u], 1u);
-        else {
-          lds[atomicAdd(&cn, 1u)] = bits;
-          atomicAdd(&L.rhist[(int64_t)v * kRefineBins + ((bits >> 8) & 255u)], 1u);
-        }
+      for (int i = 0; i < 4; ++i) {
+        const uint32_t bits = __float_as_uint(q[k][i]);
+        if (i < a[k].valid && (bits >> 16) == st.prefix) atomicAdd(&lds[(bits >> 13) & 7u], 1u);
       }
     }
-  }
-  __syncthreads();
-  if constexpr (PREC == IGSP_FP16) {
+    __syncthreads();
     if (threadIdx.x < 8 && lds[threadIdx.x])
       atomicAdd(&L.rhist[(int64_t)v * kRefineBins + threadIdx.x], lds[threadIdx.x]);
     return;
   }
-  const uint32_t n = cn;  // at most the chunk's pixels
-  if (n <= kGatherPlain) {
-    if (threadIdx.x == 0 && n) cbase = atomicAdd(&L.cand_n[v], n);
-    __syncthreads();
-    for (uint32_t k = threadIdx.x; k < n; k += 256) add_candidate(L, vd, v, cbase + k, lds[k], 1u);
+  uint32_t* const coarse = L.rhist + (int64_t)v * kRefineBins;
+  uint32_t* const fine = L.fine + (int64_t)(v - L.view0) * kFineBins;
+  auto each_candidate = [&](auto&& f) {
+#pragma unroll
+    for (int k = 0; k < kWalkUnroll; ++k) {
+      if (ck.u0 + wave + 4 * k >= ck.u1) break;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const uint32_t bits = __float_as_uint(q[k][i]);
+        if (i < a[k].valid && (bits >> 16) == st.prefix) f(bits & 0xFFFFu);
+      }
+    }
+  };
+  if (threadIdx.x == 0) cn = 0;
+  __syncthreads();
+  each_candidate([&](uint32_t low) {
+    const uint32_t at = atomicAdd(&cn, 1u);
+    if (at < kGatherFew) lds[at] = low;
+  });
+  __syncthreads();
+  const uint32_t n = cn;
+  if (n <= kGatherFew) {
+    if (threadIdx.x >= n) return;  // (n <= 64: lanes of the first wavefront)
+    const uint32_t low = lds[threadIdx.x];
+    uint32_t same = 0, near = 0;      // this lane's value and its upper 8 bits among the candidates
+    bool first = true, first_near = true;
+    for (uint32_t j = 0; j < n; ++j) {
+      const uint32_t o = lds[j];
+      const bool eq = o == low, eq_near = (o >> 8) == (low >> 8), before = j < threadIdx.x;
+      same += eq ? 1 : 0;
+      near += eq_near ? 1 : 0;
+      first = first && !(eq && before);
+      first_near = first_near && !(eq_near && before);
+    }
+    if (first) atomicAdd(fine + low, same);
+    if (first_near) atomicAdd(coarse + (low >> 8), near);
     return;
   }
-  uint32_t* const keys = lds + kGatherList;  // 0: free (a stored survivor is never 0)
-  uint32_t* const times = keys + kGatherTable;
-  for (int k = threadIdx.x; k < kGatherTable; k += 256) keys[k] = times[k] = 0;
+  uint32_t* const sums = lds + kGatherTable;
+  for (int k = threadIdx.x; k < kGatherTable + kRefineBins; k += 256) lds[k] = 0;
   __syncthreads();
-  for (uint32_t k = threadIdx.x; k < n; k += 256) {
-    const uint32_t bits = lds[k];
-    uint32_t h = (bits * 2654435761u) >> 22;
-    bool placed = false;
-    for (int probe = 0; probe < 8 && !placed; ++probe) {
-      const uint32_t prev = atomicCAS(&keys[h], 0u, bits);
-      if (prev == 0u || prev == bits) {
-        atomicAdd(&times[h], 1u);
-        placed = true;
+  each_candidate([&](uint32_t low) {
+    uint32_t h = (low * 2654435761u) >> 20;  // 12 bits: kGatherTable
+    for (;;) {
+      const uint32_t prev = atomicCAS(&lds[h], 0u, (low << 16) | 1u);
+      if (prev == 0u) break;
+      if ((prev >> 16) == low) {
+        atomicAdd(&lds[h], 1u);
+        break;
       }
       h = (h + 1) & (kGatherTable - 1);
     }
-    if (!placed) add_candidate(L, vd, v, atomicAdd(&L.cand_n[v], 1u), bits, 1u);
+  });
+  __syncthreads();
+  for (int k = threadIdx.x; k < kGatherTable; k += 256) {
+    const uint32_t e = lds[k];
+    if (e) {
+      atomicAdd(fine + (e >> 16), e & 0xFFFFu);
+      atomicAdd(&sums[e >> 24], e & 0xFFFFu);
+    }
   }
   __syncthreads();
-  for (int k = threadIdx.x; k < kGatherTable; k += 256)
-    if (keys[k]) add_candidate(L, vd, v, atomicAdd(&L.cand_n[v], 1u), keys[k], times[k]);
+  if (sums[threadIdx.x]) atomicAdd(coarse + threadIdx.x, sums[threadIdx.x]);
 }
 
-// The rest of FP32's selection (16 bits, two digits of 8) by one work-group:
-// the first digit from median_gather's counts, the second from the view's
-// candidate list, or from the stored map where the list had no room (hs: 256
-// words of LDS).
-__device__ __forceinline__ MedState resolve_view(const EdgeLaunch& L, int v, const ViewDesc& vd, MedState st, uint32_t* hs,
-                                                 uint32_t* tmp, MedState* s_st) {
+// The rest of FP32's selection by one work-group: 16 bits, two digits of 8,
+// from median_gather's counts.
+__device__ __forceinline__ MedState resolve_view(const EdgeLaunch& L, int v, MedState st, uint32_t* tmp, MedState* s_st) {
   if (st.n == 0) return st;
-  const uint32_t nc = L.cand_n[v];
-  const uint2* list = reinterpret_cast<const uint2*>(L.cand) + vd.cand_off;
-  hs[threadIdx.x] = 0;
   st = refine_step(L, st, L.rhist + (int64_t)v * kRefineBins, 8, tmp, s_st);
-  if (nc <= (uint32_t)vd.cand_cap) {
-    for (uint32_t k = threadIdx.x; k < nc; k += 256) {
-      const uint2 e = list[k];
-      if ((e.x >> 8) == st.prefix) atomicAdd(&hs[e.x & 255u], e.y);
-    }
-  } else {
-    const RowChunk all = {v, 0, strips_of(vd) * vd.H, 0};
-    refine_slots<IGSP_FP32, 4, false>(L, vd, all, st, 8, hs, __lane_id(),
-                                      __builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
-  }
-  __syncthreads();
-  return refine_step(L, st, hs, 8, tmp, s_st);
+  return refine_step(L, st, L.fine + (int64_t)(v - L.view0) * kFineBins + (st.prefix & 255u) * 256u, 8, tmp, s_st);
 }
 
 // ------------------------------------------------------------- stage 3
@@ -1341,7 +1363,7 @@ __device__ __forceinline__ void norm_slots(const EdgeLaunch& L, const ViewDesc& 
 // Normalisation of a row chunk (of at most kChunkSlots slots: one walk step
 // per wavefront, loaded before the median is known). Each work-group takes
 // the last selection step itself, from the last pass's digit counts (in the
-// short chain FP32's last two, from the candidates), and the view's first
+// short chain FP32's last two), and the view's first
 // chunk stores the final state and writes the view's outputs.
 template <int PREC, bool SHORT>
 __global__ __launch_bounds__(256) void normalise_kernel(EdgeLaunch L, int chunk0) {
@@ -1363,8 +1385,7 @@ __global__ __launch_bounds__(256) void normalise_kernel(EdgeLaunch L, int chunk0
     if constexpr (PREC == IGSP_FP16) {
       st = refine_step8(load_uniform(L.state + v), as_constant(L.rhist + v * (int64_t)kRefineBins));
     } else if constexpr (SHORT) {
-      __shared__ uint32_t hs[kRefineBins];
-      st = resolve_view(L, v, vd, load_uniform(L.state + v), hs, tmp, &s_st);
+      st = resolve_view(L, v, load_uniform(L.state + v), tmp, &s_st);
     } else {
       st = refine_step(L, load_uniform(L.state + (P - 1) * n + v), L.rhist + ((P - 1) * n + v) * kRefineBins,
                        refine_digit_bits(PREC), tmp, &s_st);

@@ -88,6 +88,7 @@ struct EdgePlan {
   int n_wide = 0;
   uint32_t* d_cand = nullptr;     // FP32: median candidates and their counts per view
   uint32_t* d_cand_n = nullptr;
+  uint32_t* d_fine = nullptr;     // FP32: the short chain's counts, of at most kFineViews views
   std::vector<int> item_begin, chunk_begin, rchunk_begin;  // per view, size n_views + 1
   void* d_map = nullptr;
   uint32_t* d_hist = nullptr;
@@ -105,7 +106,8 @@ struct EdgePlan {
   int64_t map_elems = 0;
   ~EdgePlan() {
     (void)hipFree(d_views); (void)hipFree(d_items); (void)hipFree(d_items_all); (void)hipFree(d_chunks);
-    (void)hipFree(d_rchunks); (void)hipFree(d_wide); (void)hipFree(d_cand); (void)hipFree(d_cand_n); (void)hipFree(d_map);
+    (void)hipFree(d_rchunks); (void)hipFree(d_wide); (void)hipFree(d_cand); (void)hipFree(d_cand_n); (void)hipFree(d_fine);
+    (void)hipFree(d_map);
     (void)hipFree(d_hist); (void)hipFree(d_rhist); (void)hipFree(d_state);
     (void)hipFree(d_pchunks); (void)hipFree(d_tasks); (void)hipFree(d_sync); (void)hipFree(d_ctl);
     (void)hipFree(const_cast<UfItem*>(uf.items)); (void)hipFree(uf.gray); (void)hipFree(uf.blur);
@@ -350,7 +352,9 @@ igsp_status build_edge_plan(const EdgeKey& key, std::shared_ptr<EdgePlan>* out) 
     return IGSP_ERR_HIP;
   if (hipMalloc(&plan->d_map, (size_t)std::max<int64_t>(map_elems, 64) * esz) != hipSuccess) return IGSP_ERR_HIP;
   if (cand_elems > 0 &&
-      (hipMalloc(reinterpret_cast<void**>(&plan->d_cand), (size_t)cand_elems * sizeof(uint2)) != hipSuccess ||
+      (hipMalloc(reinterpret_cast<void**>(&plan->d_cand), (size_t)cand_elems * sizeof(uint32_t)) != hipSuccess ||
+       hipMalloc(reinterpret_cast<void**>(&plan->d_fine),
+                 (size_t)std::min(n, kFineViews) * kFineBins * sizeof(uint32_t)) != hipSuccess ||
        hipMalloc(reinterpret_cast<void**>(&plan->d_cand_n), (size_t)n * sizeof(uint32_t)) != hipSuccess))
     return IGSP_ERR_HIP;
   // refinement histograms of up to two passes, selection states after 0, 1
@@ -510,15 +514,18 @@ igsp_status get_edge_plan(const igsp_view* views, int32_t n_views, const igsp_ed
 
 // Whether the stages of views [v0, v1) take the short median chain (FP32,
 // FP16). It saves two (FP32) launches of 4 us, but every work-group then
-// selects from its view's whole first histogram and list: measured about
-// 3 ns a chunk and 1/80 ns more for each chunk of the same view (the list
-// grows with the view), against 8 us saved; FP16 costs and saves half. Short
-// against long, FP32: one 1297x840 view (293 chunks) 32.5 and 37.9 us, two
-// 40.3 and 45.4, four (1180) 54.2 and 52.8, one 2473x1643 (929) 57.4 and
-// 52.0, 64 views of 300x187 (1491) 52.4 and 55.4, 200 of them 95.7 and 89.3;
-// FP16: 27.1 and 29.5, 30.0 and 32.3, 38.3 and 41.6, 44.1 and 41.3, 44.5 and
-// 47.0, 84.3 and 80.9.
+// selects from its view's whole first histogram: about 3 ns a chunk and 1/80
+// ns more for each chunk of the same view, against 8 us saved; FP16 costs and
+// saves half. Short against long, FP32: one 1297x840 view (293 chunks) 25.6
+// and 33.1 us, two 31.0 and 40.0, four (1180) 38.0 and 45.6, one 1984x1376
+// (688) 35.3 and 43.7, one 2473x1643 (929) 41.5 and 48.1, 64 views of 300x187
+// (1491) 42.7 and 45.7; FP16: 23.9 and 25.0, 28.1 and 29.8, 35.2 and 37.6,
+// 33.9 and 32.6, 42.8 and 39.1, 37.1 and 39.2, 200 of 300x187 77.6 and 72.7.
+// (FP32 alone would gain a little above the line too; a view whose stripes
+// have thousands of different magnitudes in one bucket, the worst for the
+// short chain's counts, does not: 1984x1376 62 and 54.)
 bool short_chain(const EdgePlan& P, int v0, int v1) {
+  if (P.key.precision == IGSP_FP32 && (v1 - v0 > kFineViews || !P.d_fine)) return false;
   int64_t cost = 0;
   for (int v = v0; v < v1 && cost <= 80 * 8000; ++v) {
     const int64_t c = P.chunk_begin[v + 1] - P.chunk_begin[v];
@@ -542,6 +549,8 @@ igsp_status enqueue_edge(EdgePlan* P, const uint8_t* images, int64_t img_end, fl
   L.state = P->d_state;
   L.cand = P->d_cand;
   L.cand_n = P->d_cand_n;
+  L.fine = P->d_fine;
+  L.view0 = 0;
   L.use_cand = 0;
   L.refine_slots = kRefineChunkSlots;
   L.short_chain = 0;
@@ -565,7 +574,11 @@ igsp_status enqueue_edge(EdgePlan* P, const uint8_t* images, int64_t img_end, fl
   // median selection (+ refinement passes) of views [v0, v1); the last
   // selection step is taken by the normalisation
   auto tail = [&](int v0, int v1, hipStream_t st) -> hipError_t {
-    if (is_short(v0, v1)) return launch_median_gather(L, P->chunk_begin[v0], P->chunk_begin[v1] - P->chunk_begin[v0], st);
+    if (is_short(v0, v1)) {
+      EdgeLaunch LA = L;
+      LA.view0 = v0;
+      return launch_median_gather(LA, P->chunk_begin[v0], P->chunk_begin[v1] - P->chunk_begin[v0], st);
+    }
     const bool wide = P->n_wide > 0 && v0 == 0 && v1 == n;
     const int f0 = wide ? 0 : P->rchunk_begin[v0], f1 = wide ? P->n_wide : P->rchunk_begin[v1];
     EdgeLaunch LR = L;
@@ -583,12 +596,14 @@ igsp_status enqueue_edge(EdgePlan* P, const uint8_t* images, int64_t img_end, fl
   auto stencil = [&](int v0, int v1, hipStream_t st) -> hipError_t {
     EdgeLaunch LA = L;
     LA.short_chain = is_short(v0, v1);
+    LA.view0 = v0;
     if (v0 == 0 && v1 == n) LA.items = P->d_items_all;
     return launch_edge_fused(LA, P->item_begin[v0], P->item_begin[v1] - P->item_begin[v0], st);
   };
   auto norm = [&](int v0, int v1, hipStream_t st) -> hipError_t {
     EdgeLaunch LA = L;
     LA.short_chain = is_short(v0, v1);
+    LA.view0 = v0;
     return launch_normalise(LA, P->chunk_begin[v0], P->chunk_begin[v1] - P->chunk_begin[v0], st);
   };
   hipError_t e = mark(0, s);

@@ -46,6 +46,11 @@ constexpr int kRefineBins = 256;          // radix digit of the refine passes
 constexpr int kRefineChunkSlots = 64;
 constexpr int kRefineWideSlots = 128;
 constexpr int64_t kWideSlots = 40000;
+// FP32's short median chain: counts of the 16 bits that the first histogram
+// leaves open (256 KiB a view), and the most views of a launch that takes it
+// (16 MiB of counts to clear, about 3 us).
+constexpr int kFineBins = 1 << 16;
+constexpr int kFineViews = 64;
 // Slots (248 pixels each) per work-group of the other element-wise passes,
 // about 4 Ki pixels (measured best for normalisation).
 constexpr int kChunkSlots = 16;
@@ -107,11 +112,12 @@ struct EdgeLaunch {
   uint32_t* hist;            // [n_views][kBinsMax]
   uint32_t* rhist;           // [2][n_views][kRefineBins]: refinement pass p's digit histograms
   MedState* state;           // [3][n_views]: the selection state after p refinement steps
-  uint32_t* cand;            // FP32: survivors in the first histogram's median bucket, per view (short chain:
-                             // pairs of value and count)
+  uint32_t* cand;            // FP32: survivors in the first histogram's median bucket, per view
   uint32_t* cand_n;          // [n_views]: candidates found (more than the room: list not used)
   int refine_slots;          // slots per chunk of this refinement launch
   int use_cand;              // the refinement passes of this launch use the candidate lists
+  uint32_t* fine;            // FP32, short chain: [views of the launch][kFineBins] counts of the open 16 bits
+  int view0;                 // first view of the launch (short chain)
   int short_chain;           // the median takes one launch (median_gather) before the normalisation
   float* medians_dn;         // optional outputs
   int32_t* survivors;

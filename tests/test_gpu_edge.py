@@ -297,3 +297,26 @@ def test_ties_and_segment_remainders(precision, seg_rows):
         assert np.array_equal(view_map(a, vb, v), view_map(b, vb, v)), v
     assert np.array_equal(ma, mb) and np.array_equal(na, nb) and (na > 0).all()
     check_batch(vb, precision, "plain", views=[0, 13, 16])
+
+
+@pytest.mark.parametrize("n_views", [1, 64, 65])
+def test_fp32_short_chain_equal_and_distinct_values(n_views):
+    """The short chain counts the median bucket's values after merging equal
+    ones: 6-pixel stripes have one magnitude (thousands of candidates a chunk,
+    all equal), with sensor noise they have thousands of different ones, and a
+    textured view has a few. 64 views are the most that one FP32 launch counts
+    this way. All equal the unfused form, which never does, bit for bit."""
+    rng = np.random.default_rng(7)
+    imgs = []
+    for k in range(n_views):
+        h, w = (300, 500) if k < 3 else (20 + k % 7, 30 + k % 5)
+        im = np.zeros((h, w, 3)) + ((((np.arange(w) // 3) % 2) * 180) + 30)[None, :, None]
+        if k % 3 != 1:
+            im = im + rng.normal(0, 1.0, (h, w, 1))
+        imgs.append(np.clip(np.rint(im), 0, 255).astype(np.uint8) if k % 3 != 2 else synth.image(70 + k, w, h, n_poly=10, texture=True))
+    vb = synth.pack_views(imgs, in_align=1, out_align=4)
+    a, ma, na = gpu_edge(vb, "fp32", "staged", reps=3)
+    p, mp, np_ = gpu_edge(vb, "fp32", "plain", reps=2)
+    b, mb, nb = gpu_edge(vb, "fp32", "unfused")
+    assert np.array_equal(a, b) and np.array_equal(ma, mb) and np.array_equal(na, nb) and (na > 0).any()
+    assert np.array_equal(p, b) and np.array_equal(mp, mb) and np.array_equal(np_, nb)
