@@ -817,9 +817,9 @@ igsp_status get_sel_plan(const igsp_view* views, int32_t n_views, int64_t capaci
   // (the histogram and the list's length are cleared by each call's first
   // kernel, so the plan needs no memset)
   if (upload(&plan->d_views, sv) != hipSuccess ||
-      hipMalloc(reinterpret_cast<void**>(&plan->d_hist), kSelBins * sizeof(uint32_t)) != hipSuccess ||
+      hipMalloc(reinterpret_cast<void**>(&plan->d_hist), kSelLevels * kSelBins * sizeof(uint32_t)) != hipSuccess ||
       hipMalloc(reinterpret_cast<void**>(&plan->d_counts), tiles * sizeof(uint32_t)) != hipSuccess ||
-      hipMalloc(reinterpret_cast<void**>(&plan->d_state), sizeof(SelState)) != hipSuccess ||
+      hipMalloc(reinterpret_cast<void**>(&plan->d_state), kSelLevels * sizeof(SelState)) != hipSuccess ||
       hipMalloc(reinterpret_cast<void**>(&plan->d_ckeys), std::max<int64_t>(capacity, 1) * sizeof(uint64_t)) !=
           hipSuccess ||
       hipMalloc(reinterpret_cast<void**>(&plan->d_crows), std::max<int64_t>(capacity, 1) * sizeof(int32_t)) !=

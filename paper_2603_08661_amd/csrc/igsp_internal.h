@@ -262,14 +262,22 @@ struct SelView {
 constexpr int kSelBins = 4096;
 constexpr int kSelHistGrid = 512;      // its work-groups (each clears and flushes a histogram)
 
-enum : int32_t { kSelDone = 0, kSelList = 1, kSelTie = 2 };
+// The first histogram's level, then the refinements of a group too long to list.
+constexpr int kSelLevels = 3;
 
-struct SelState {      // device scalars of one selection, after sel_collect
-  int64_t need;        // rows of the K-th key's bin to take
+enum : int32_t { kSelDone = 0, kSelList = 1, kSelTie = 2, kSelWide = 3, kSelLast = 4 };
+
+struct SelState {      // device scalars of one selection after a level
+  int64_t need;        // rows of the group to take
+  int64_t in;          // rows of the group
+  uint64_t prefix;     // the bits above `shift` that the group's keys share
   int64_t last;        // kSelTie: the last row taken
-  int32_t bin;
-  int32_t mode;        // kSelDone: the bin is taken whole; kSelList: its rows are listed;
-                       // kSelTie: they share one key, counted per tile
+  uint64_t least;      // kSelLast: smallest and largest key of the group
+  uint64_t most;
+  int32_t shift;
+  int32_t mode;        // kSelDone: the group is taken whole; kSelList: its rows are listed; kSelTie: they share
+                       // one key, counted per tile; kSelWide: their next digit is counted; kSelLast: both
+                       // listed and counted per tile
   uint32_t listed;
   uint32_t pad;
 };
@@ -292,11 +300,11 @@ struct SelLaunch {
   uint8_t* mask;
   int64_t* scores;
   int64_t* n_selected;
-  uint32_t* hist;           // [kSelBins]
+  uint32_t* hist;           // [kSelLevels][kSelBins]
   uint64_t* ckeys;          // [capacity]: keys and rows of the K-th key's bin, in any order
   int32_t* crows;
   uint32_t* tile_counts;    // [tiles]
-  SelState* state;
+  SelState* state;          // [kSelLevels]
   int grid;
 };
 

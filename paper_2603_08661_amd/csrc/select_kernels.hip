@@ -18,6 +18,10 @@
 //                 rows above the bin are selected, rows inside it listed (or,
 //                 where the bin is one exact key shared by more rows than are
 //                 still to take, counted per tile)
+//   sel_refine  : (twice) where that list would be long, because most scores
+//                 lie within 1.6% of each other, the next 12 bits are counted
+//                 instead, by all work-groups, and the rows of the K-th key's
+//                 digit listed (or counted on); nothing to do otherwise
 //   sel_finish  : one work-group: exact selection among the listed keys, ties
 //                 by lower index; or the last row of a tie from the tile counts
 //   sel_ties    : the rows of such a tie (nothing to do otherwise)
@@ -44,8 +48,12 @@ __global__ __launch_bounds__(kSelThreads) void sel_clear_kernel(SelLaunch S) {
   for (int64_t g = (int64_t)blockIdx.x * kSelThreads + threadIdx.x; g < N; g += (int64_t)gridDim.x * kSelThreads)
     S.scores[g] = 0;
   if (blockIdx.x == 0) {
-    for (int i = threadIdx.x; i < kSelBins; i += kSelThreads) S.hist[i] = 0;
-    if (threadIdx.x == 0) S.state->listed = 0;
+    for (int i = threadIdx.x; i < kSelLevels * kSelBins; i += kSelThreads) S.hist[i] = 0;
+    if (threadIdx.x < kSelLevels) {
+      S.state[threadIdx.x].listed = 0;
+      S.state[threadIdx.x].least = ~0ull;
+      S.state[threadIdx.x].most = 0;
+    }
   }
 }
 
@@ -259,16 +267,19 @@ __global__ __launch_bounds__(kSelThreads) void sel_hist_kernel(SelLaunch S) {
   }
 }
 
-// What is left to select once the first histogram is known; every work-group
-// of sel_collect takes this step alike.
+// What is left to select once a histogram is known; every work-group takes
+// this step alike.
 struct SelPick {
-  int64_t k;       // Gaussians to select
+  int64_t k;       // Gaussians to select from the whole histogram
   int64_t need;    // of them, inside the bin
   int64_t in_bin;  // candidates inside the bin
   int bin;
 };
 
-__device__ __forceinline__ SelPick pick_bin(const SelLaunch& S, int64_t N, uint32_t* wsum, SelPick* s_pick) {
+// The bin of the K-th largest entry; K = want, or (want < 0) what the budget
+// leaves room for.
+__device__ __forceinline__ SelPick pick_bin(const SelLaunch& S, const uint32_t* hist, int64_t N, int64_t want,
+                                            uint32_t* wsum, SelPick* s_pick) {
   constexpr int PER = kSelBins / kSelThreads;
   static_assert(kSelBins % kSelThreads == 0 && PER % 4 == 0, "whole 16-byte words of bins per thread");
   // descending order: thread t holds the bins from kSelBins - 1 - t PER down
@@ -277,13 +288,13 @@ __device__ __forceinline__ SelPick pick_bin(const SelLaunch& S, int64_t N, uint3
   uint32_t sum = 0;
 #pragma unroll
   for (int j = 0; j < PER / 4; ++j) {
-    const uint4 q = reinterpret_cast<const uint4*>(S.hist + lo)[j];
+    const uint4 q = reinterpret_cast<const uint4*>(hist + lo)[j];
     c[4 * j] = q.x; c[4 * j + 1] = q.y; c[4 * j + 2] = q.z; c[4 * j + 3] = q.w;
     sum += q.x + q.y + q.z + q.w;
   }
   uint32_t total = 0;
   int64_t above = sel_scan(sum, wsum, total);
-  const int64_t room = S.budget > N ? S.budget - N : 0;
+  const int64_t room = want >= 0 ? want : (S.budget > N ? S.budget - N : 0);
   const int64_t K = (int64_t)total < room ? (int64_t)total : room;
   if (K == 0) {
     if (threadIdx.x == 0) *s_pick = SelPick{0, 0, 0, kSelBins};
@@ -302,27 +313,47 @@ __device__ __forceinline__ SelPick pick_bin(const SelLaunch& S, int64_t N, uint3
   return *s_pick;
 }
 
-// LDS list of a tile's rows inside the bin.
-__global__ __launch_bounds__(kSelThreads) void sel_collect_kernel(SelLaunch S) {
-  __shared__ uint32_t wsum[kSelThreads / 64];
-  __shared__ SelPick s_pick;
-  __shared__ uint64_t lkey[kSelTile];
-  __shared__ int32_t lrow[kSelTile];
-  __shared__ uint32_t ln, lbase;
-  const int64_t N = live_count(S);
+// How the rest of a group of rows is selected: its keys share the bits above
+// `shift`, `need` of its `in` rows are taken. A list is finished by one
+// work-group, so a long one is refined first: 3M scores within 1%, 0.6M of
+// them taken, 7.4 ms with the list alone.
+constexpr int64_t kSelLongList = 8192;
+
+__device__ __forceinline__ int group_mode(int64_t need, int64_t in, int shift, int level) {
+  if (need == in) return kSelDone;
+  if (shift == 0) return kSelTie;
+  if (in <= kSelLongList) return kSelList;
+  return level + 1 < kSelLevels ? kSelWide : kSelLast;
+}
+
+// Work-group state of a pass over the rows: a tile's listed rows, or the
+// digit histogram of the work-group's tiles.
+struct SelLds {
+  union {
+    uint64_t key[kSelTile];
+    uint32_t hist[kSelBins];
+  };
+  int32_t row[kSelTile];
+  uint32_t n, base;
+};
+static_assert(kSelBins * sizeof(uint32_t) <= kSelTile * sizeof(uint64_t), "the histogram fits the keys");
+
+constexpr int kSelDigit = 12;
+static_assert((1 << kSelDigit) == kSelBins, "a digit is a bin");
+
+// A pass over the rows: `above(key)` rows are selected (the mask is written
+// for every row, or only for those: WRITE), rows of the group (key >> shift ==
+// prefix) counted or listed as `mode` says, for level `level`.
+template <bool WRITE, class Above>
+__device__ __forceinline__ void sel_pass(const SelLaunch& S, int64_t N, int level, int mode, uint64_t prefix, int shift,
+                                         SelLds& l, uint32_t* wsum, Above above) {
+  SelState* const st = S.state + level;
   const int64_t nt = (N + kSelTile - 1) / kSelTile;
-  if ((int64_t)blockIdx.x >= nt && blockIdx.x > 0) return;
-  const SelPick p = pick_bin(S, N, wsum, &s_pick);
-  const bool all = p.need == p.in_bin;                    // the whole bin (or nothing) is taken
-  const bool tie = !all && open_bits(p.bin) == 0;         // some of the rows of one key
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    S.state->need = p.need;
-    S.state->bin = p.bin;
-    S.state->mode = all ? kSelDone : (tie ? kSelTie : kSelList);
-    if (S.n_selected) *S.n_selected = p.k;
-  }
-  const int least = all ? p.bin : p.bin + 1;              // bins selected as a whole
-  if (threadIdx.x == 0) ln = 0;
+  const int bits = shift < kSelDigit ? shift : kSelDigit;
+  uint64_t least = ~0ull, most = 0;
+  if (mode == kSelWide)
+    for (int i = threadIdx.x; i < kSelBins; i += kSelThreads) l.hist[i] = 0;
+  if (threadIdx.x == 0) l.n = 0;
   __syncthreads();
   for (int64_t t = blockIdx.x; t < nt; t += gridDim.x) {
     uint64_t key[kSelUnroll];
@@ -330,39 +361,114 @@ __global__ __launch_bounds__(kSelThreads) void sel_collect_kernel(SelLaunch S) {
     uint32_t ties = 0;
 #pragma unroll
     for (int k = 0; k < kSelUnroll; ++k) {
-      const int r = k * kSelThreads + threadIdx.x;
-      const int64_t g = t * kSelTile + r;
-      const int bin = key[k] ? key_bin(key[k]) : -1;
-      if (g < N) S.mask[g] = (uint8_t)(bin >= least);
-      if (!all && bin == p.bin) {
-        if (tie) {
-          ++ties;
-        } else {
-          const uint32_t at = atomicAdd(&ln, 1u);
-          lkey[at] = key[k];
-          lrow[at] = (int32_t)g;
-        }
+      const int64_t g = t * kSelTile + k * kSelThreads + threadIdx.x;
+      const bool up = key[k] && above(key[k]);
+      if (g < N && (WRITE || up)) S.mask[g] = (uint8_t)up;
+      if (mode == kSelDone || !key[k] || (key[k] >> shift) != prefix) continue;
+      if (mode == kSelTie || mode == kSelLast) ++ties;
+      if (mode == kSelWide) atomicAdd(&l.hist[(uint32_t)(key[k] >> (shift - bits)) & ((1u << bits) - 1u)], 1u);
+      if (mode == kSelList || mode == kSelLast) {
+        const uint32_t at = atomicAdd(&l.n, 1u);
+        l.key[at] = key[k];
+        l.row[at] = (int32_t)g;
+        least = key[k] < least ? key[k] : least;
+        most = key[k] > most ? key[k] : most;
       }
     }
-    if (all) continue;  // uniform
-    if (tie) {
+    if (mode == kSelDone || mode == kSelWide) continue;  // uniform
+    if (mode == kSelTie || mode == kSelLast) {
       uint32_t total = 0;
       (void)sel_scan(ties, wsum, total);
       if (threadIdx.x == 0) S.tile_counts[t] = total;
-      continue;
+      if (mode == kSelTie) continue;
     }
     __syncthreads();
-    if (threadIdx.x == 0 && ln) lbase = atomicAdd(&S.state->listed, ln);
+    if (threadIdx.x == 0 && l.n) l.base = atomicAdd(&st->listed, l.n);
     __syncthreads();
-    const uint32_t n = ln;
+    const uint32_t n = l.n;
     for (uint32_t i = threadIdx.x; i < n; i += kSelThreads) {
-      S.ckeys[lbase + i] = lkey[i];
-      S.crows[lbase + i] = lrow[i];
+      S.ckeys[l.base + i] = l.key[i];
+      S.crows[l.base + i] = l.row[i];
     }
     __syncthreads();
-    if (threadIdx.x == 0) ln = 0;
+    if (threadIdx.x == 0) l.n = 0;
     __syncthreads();
   }
+  if (mode == kSelWide) {
+    __syncthreads();
+    for (int i = threadIdx.x; i < kSelBins; i += kSelThreads) {
+      const uint32_t c = l.hist[i];
+      if (c) atomicAdd(&S.hist[(level + 1) * kSelBins + i], c);
+    }
+  }
+  if (mode == kSelLast) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      const uint64_t a = (uint64_t)__shfl_xor((unsigned long long)least, o, 64);
+      const uint64_t b = (uint64_t)__shfl_xor((unsigned long long)most, o, 64);
+      least = a < least ? a : least;
+      most = b > most ? b : most;
+    }
+    if ((threadIdx.x & 63) == 0 && most) {
+      atomicMin(reinterpret_cast<unsigned long long*>(&st->least), (unsigned long long)least);
+      atomicMax(reinterpret_cast<unsigned long long*>(&st->most), (unsigned long long)most);
+    }
+  }
+}
+
+__device__ __forceinline__ void put_group(SelState* st, int64_t need, int64_t in, uint64_t prefix, int shift, int mode) {
+  st->need = need;
+  st->in = in;
+  st->prefix = prefix;
+  st->shift = shift;
+  st->mode = mode;
+}
+
+__global__ __launch_bounds__(kSelThreads) void sel_collect_kernel(SelLaunch S) {
+  __shared__ uint32_t wsum[kSelThreads / 64];
+  __shared__ SelPick s_pick;
+  __shared__ SelLds l;
+  const int64_t N = live_count(S);
+  const int64_t nt = (N + kSelTile - 1) / kSelTile;
+  if ((int64_t)blockIdx.x >= nt && blockIdx.x > 0) return;
+  const SelPick p = pick_bin(S, S.hist, N, -1, wsum, &s_pick);
+  const int shift = open_bits(p.bin);
+  const uint64_t prefix = p.bin < 128 ? (uint64_t)p.bin : (uint64_t)(64 + (p.bin & 63));
+  const int mode = group_mode(p.need, p.in_bin, shift, 0);
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    put_group(S.state, p.need, p.in_bin, prefix, shift, mode);
+    if (S.n_selected) *S.n_selected = p.k;
+  }
+  const int least = mode == kSelDone ? p.bin : p.bin + 1;              // bins selected as a whole
+  sel_pass<true>(S, N, 0, mode, prefix, shift, l, wsum, [&](uint64_t key) { return key_bin(key) >= least; });
+}
+
+// The next digit of a group whose list would be long.
+__global__ __launch_bounds__(kSelThreads) void sel_refine_kernel(SelLaunch S, int level) {
+  __shared__ uint32_t wsum[kSelThreads / 64];
+  __shared__ SelPick s_pick;
+  __shared__ SelLds l;
+  const SelState* const from = S.state + level - 1;
+  const int old = from->mode;
+  if (old != kSelWide) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+      put_group(S.state + level, from->need, from->in, from->prefix, from->shift, old);
+      S.state[level].listed = from->listed;
+    }
+    return;
+  }
+  const int64_t N = live_count(S);
+  const int64_t nt = (N + kSelTile - 1) / kSelTile;
+  if ((int64_t)blockIdx.x >= nt && blockIdx.x > 0) return;
+  const uint64_t prefix0 = from->prefix;
+  const int shift0 = from->shift, bits = shift0 < kSelDigit ? shift0 : kSelDigit, shift = shift0 - bits;
+  const SelPick p = pick_bin(S, S.hist + level * kSelBins, N, from->need, wsum, &s_pick);
+  const uint64_t prefix = (prefix0 << bits) | (uint64_t)p.bin;
+  const int mode = group_mode(p.need, p.in_bin, shift, level);
+  if (blockIdx.x == 0 && threadIdx.x == 0) put_group(S.state + level, p.need, p.in_bin, prefix, shift, mode);
+  const uint64_t least = mode == kSelDone ? prefix : prefix + 1;
+  sel_pass<false>(S, N, level, mode, prefix, shift, l, wsum,
+                  [&](uint64_t key) { return (key >> shift0) == prefix0 && (key >> shift) >= least; });
 }
 
 // One work-group of kFinThreads threads. A digit of kFinBits bits per pass.
@@ -421,20 +527,33 @@ __device__ __forceinline__ uint32_t fin_pass(uint32_t n, Match match, Digit digi
 
 // The rest of the selection, by one work-group. Bound by latency: a list is
 // the candidates of 1/64 of an octave of scores (about 5,000 for 1.2M of 3M
-// Gaussians), 2 passes of 2 us; a list of every candidate (all scores within
-// 1.5%) would take about 0.2 ms a pass for 1.2M entries.
+// Gaussians), 2 passes of 2 us, or at most kSelLongList. (Longer only after
+// both refinements, where more rows than that agree in 30 bits and are still
+// not all equal: about 2.4 ms a pass for 3M rows.)
 __global__ __launch_bounds__(kFinThreads) void sel_finish_kernel(SelLaunch S) {
   __shared__ uint32_t h[kFinBins];
   __shared__ uint32_t wsum[kFinThreads / 64];
   __shared__ int64_t pick[3];
-  const int mode = S.state->mode;
-  int64_t need = S.state->need;
+  SelState* const st = S.state + kSelLevels - 1;
+  int mode = st->mode;
+  int64_t need = st->need;
+  uint64_t key = st->prefix;  // kSelTie: the one key
+  if (mode == kSelLast) {
+    const bool one = st->least == st->most;
+    if (one) key = st->least;
+    mode = one ? kSelTie : kSelList;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      st->mode = mode;
+      st->prefix = key;
+    }
+  }
   if (mode == kSelList) {
-    const uint32_t n = S.state->listed;
+    const uint32_t n = st->listed;
     const uint64_t* keys = S.ckeys;
     const int32_t* rows = S.crows;
-    int shift = open_bits(S.state->bin);
-    uint64_t prefix = n ? keys[0] >> shift : 0;  // the bits that every key of the bin shares
+    int shift = st->shift;
+    uint64_t prefix = key;  // the bits that every key of the list shares
     uint32_t in = n;
     while (shift > 0 && need < (int64_t)in) {
       const int bits = min(shift, kFinBits), s = shift - bits;
@@ -484,20 +603,20 @@ __global__ __launch_bounds__(kFinThreads) void sel_finish_kernel(SelLaunch S) {
       }
     }
     __syncthreads();
-    const uint64_t key = (uint64_t)S.state->bin;  // a bin below 128 is one exact key
     const int64_t g0 = pick[0] * kSelTile + 2 * threadIdx.x;
     const bool a = g0 < N && key_of(S, g0) == key, b = g0 + 1 < N && key_of(S, g0 + 1) == key;
     const int64_t r = (int64_t)fin_scan((a ? 1u : 0u) + (b ? 1u : 0u), wsum), want = pick[1];
-    if (a && r + 1 == want) S.state->last = g0;
-    if (b && r + (a ? 2 : 1) == want) S.state->last = g0 + 1;
+    if (a && r + 1 == want) st->last = g0;
+    if (b && r + (a ? 2 : 1) == want) st->last = g0 + 1;
   }
 }
 
 // The tied rows up to the last one taken.
 __global__ __launch_bounds__(kSelThreads) void sel_ties_kernel(SelLaunch S) {
-  if (S.state->mode != kSelTie) return;
-  const int64_t last = S.state->last;
-  const uint64_t key = (uint64_t)S.state->bin;
+  const SelState* const st = S.state + kSelLevels - 1;
+  if (st->mode != kSelTie) return;
+  const int64_t last = st->last;
+  const uint64_t key = st->prefix;
   for (int64_t g = (int64_t)blockIdx.x * kSelThreads + threadIdx.x; g <= last; g += (int64_t)gridDim.x * kSelThreads)
     if (key_of(S, g) == key) S.mask[g] = 1;
 }
@@ -544,6 +663,8 @@ hipError_t launch_select(const SelLaunch& S, hipStream_t s) {
   }
   hipLaunchKernelGGL(sel_hist_kernel, dim3(grid < kSelHistGrid ? grid : kSelHistGrid), dim3(kSelThreads), 0, s, S);
   hipLaunchKernelGGL(sel_collect_kernel, dim3(grid), dim3(kSelThreads), 0, s, S);
+  for (int level = 1; level < kSelLevels; ++level)
+    hipLaunchKernelGGL(sel_refine_kernel, dim3(grid), dim3(kSelThreads), 0, s, S, level);
   hipLaunchKernelGGL(sel_finish_kernel, dim3(1), dim3(kFinThreads), 0, s, S);
   hipLaunchKernelGGL(sel_ties_kernel, dim3(grid), dim3(kSelThreads), 0, s, S);
   return hipGetLastError();

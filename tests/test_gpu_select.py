@@ -159,3 +159,27 @@ def test_split_mask_bins(N, keys):
     top = int(((scores == scores.max()) & (grad >= 0.5)).sum())
     for K in (1, top, top + 1, cand // 2, cand - 1, cand):
         run(N, N + 3, W, H, c, grad, 0.5, False, N + K, maps, off)
+
+
+@pytest.mark.parametrize("N", [12_000, 70_001])
+@pytest.mark.parametrize("keys", ["equal", "last_bit", "near", "mass_and_near"])
+def test_split_mask_concentrated_scores(N, keys):
+    """More rows in the K-th key's bin than a list is made of: keys of 41 bits
+    that are all equal, that differ in the lowest bit alone (below both
+    refined digits), that spread over 1%, and half equal, half spread. K falls
+    on the group's edges and inside it."""
+    i = np.arange(N)
+    first = {"equal": np.full(N, 256.0), "last_bit": np.full(N, 256.0), "near": 256.0 + (i * 7919 % N) * (2.5 / N),
+             "mass_and_near": np.where(i % 2 == 0, 257.0, 256.0 + (i * 7919 % N) * (2.5 / N))}[keys]
+    extra = i[i % 3 == 0] if keys == "last_bit" else i[:0]
+    g = np.concatenate([i, extra]).astype(np.int32)
+    w = np.concatenate([first, np.full(extra.size, 2.0 ** -32)]).astype(np.float32)
+    W, H, off = [3], [3], np.zeros(1, np.int64)
+    maps = np.ones(9, np.float32)
+    c = synth.Contributions(g, np.zeros(g.size, np.int32), np.full(g.size, 4, np.int32), w)
+    grad = np.where(i % 10 == 0, 0.1, 1.0).astype(np.float32)
+    cand = int((grad >= 0.5).sum())
+    scores = oracle.split_scores(maps, W, H, off, c.gauss, c.view, c.pixel, c.weight, N)
+    top = int(((scores == scores.max()) & (grad >= 0.5)).sum())
+    for K in sorted({1, top, min(top + 1, cand), cand // 3, cand // 2, cand - 1, cand}):
+        run(N, N + 3, W, H, c, grad, 0.5, False, N + K, maps, off)
