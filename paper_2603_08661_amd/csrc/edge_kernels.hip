@@ -1103,12 +1103,12 @@ __device__ __forceinline__ MedState refine_step8(const MedState& st, cptr<uint32
 // work-groups finish the selection from those counts, and its first chunk of a view
 // clears the histogram. A 256x192 FP32 view's edge maps: 35.9 us with five
 // launches, 25.0 with these three (19.7 with its segments split and their
-// first rows made cheap); 1297x840: 40.7 and 32.0 (27.5). Latency-bound: the
+// first rows made cheap); 1297x840: 40.7 and 32.0 (24.9). Latency-bound: the
 // stencil's lone wavefronts take 9-13 us, the other two launches 5-8 us each.
 // Sums of
 // the histogram over whole binades, for median_gather to read instead of its
 // 7424 bins, cost the stencil more than they saved: every work-group adds to
-// the same few words, about 100 ns an addition (1297x840: 28.4 -> 69.4 us).
+// the same few words (1297x840: 28.4 -> 69.4 us).
 
 // The state after the first histogram, taken by a whole work-group (bins: its
 // LDS copy; each thread sums PER consecutive bins, an odd number, so the reads

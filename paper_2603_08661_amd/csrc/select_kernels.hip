@@ -316,7 +316,8 @@ __device__ __forceinline__ SelPick pick_bin(const SelLaunch& S, const uint32_t* 
 // How the rest of a group of rows is selected: its keys share the bits above
 // `shift`, `need` of its `in` rows are taken. A list is finished by one
 // work-group, so a long one is refined first: 3M scores within 1%, 0.6M of
-// them taken, 7.4 ms with the list alone.
+// them taken, 7.4 ms with the list alone and 0.18 refined; all equal, 17.9 and
+// 0.29.
 constexpr int64_t kSelLongList = 8192;
 
 __device__ __forceinline__ int group_mode(int64_t need, int64_t in, int shift, int level) {
