@@ -784,11 +784,12 @@ struct SelPlan {
   uint32_t* d_hist = nullptr;
   uint32_t* d_counts = nullptr;
   SelState* d_state = nullptr;
+  SelRange* d_ranges = nullptr;
   uint64_t* d_ckeys = nullptr;
   int32_t* d_crows = nullptr;
   ~SelPlan() {
     (void)hipFree(d_views); (void)hipFree(d_hist); (void)hipFree(d_counts);
-    (void)hipFree(d_state); (void)hipFree(d_ckeys); (void)hipFree(d_crows);
+    (void)hipFree(d_state); (void)hipFree(d_ranges); (void)hipFree(d_ckeys); (void)hipFree(d_crows);
   }
 };
 std::list<std::shared_ptr<SelPlan>> g_sel_plans;
@@ -814,12 +815,13 @@ igsp_status get_sel_plan(const igsp_view* views, int32_t n_views, int64_t capaci
   std::vector<SelView> sv(n_views);
   for (int v = 0; v < n_views; ++v) sv[v] = SelView{views[v].out_offset, (int64_t)views[v].width * views[v].height};
   const int64_t tiles = std::max<int64_t>(1, (capacity + kSelTile - 1) / kSelTile);
-  // (the histogram and the list's length are cleared by each call's first
+  // (the histograms and the lists' lengths are cleared by each call's first
   // kernel, so the plan needs no memset)
   if (upload(&plan->d_views, sv) != hipSuccess ||
       hipMalloc(reinterpret_cast<void**>(&plan->d_hist), kSelLevels * kSelBins * sizeof(uint32_t)) != hipSuccess ||
       hipMalloc(reinterpret_cast<void**>(&plan->d_counts), tiles * sizeof(uint32_t)) != hipSuccess ||
       hipMalloc(reinterpret_cast<void**>(&plan->d_state), kSelLevels * sizeof(SelState)) != hipSuccess ||
+      hipMalloc(reinterpret_cast<void**>(&plan->d_ranges), kSelLevels * kSelGrid * sizeof(SelRange)) != hipSuccess ||
       hipMalloc(reinterpret_cast<void**>(&plan->d_ckeys), std::max<int64_t>(capacity, 1) * sizeof(uint64_t)) !=
           hipSuccess ||
       hipMalloc(reinterpret_cast<void**>(&plan->d_crows), std::max<int64_t>(capacity, 1) * sizeof(int32_t)) !=
@@ -867,6 +869,7 @@ extern "C" igsp_status split_mask(const float* maps, const igsp_view* views, int
   S.hist = plan->d_hist;
   S.tile_counts = plan->d_counts;
   S.state = plan->d_state;
+  S.ranges = plan->d_ranges;
   S.ckeys = plan->d_ckeys;
   S.crows = plan->d_crows;
   const int64_t tiles = std::max<int64_t>(1, (capacity + kSelTile - 1) / kSelTile);

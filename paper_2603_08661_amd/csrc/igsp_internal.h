@@ -248,7 +248,7 @@ hipError_t launch_las(const LasLaunch& L, hipStream_t s);
 // ---------------------------------------------------------------- split mask
 
 constexpr int kSelThreads = 256;
-constexpr int kSelTile = 2048;         // rows per tile of the count / mask kernels
+constexpr int kSelTile = 2048;         // rows per tile of the passes over the rows
 constexpr int kSelGrid = 1024;         // work-groups of the grid-stride kernels
 constexpr int kSelScatterGrid = 2048;  // work-groups of the contribution scatter (8 waves per SIMD)
 
@@ -263,7 +263,7 @@ constexpr int kSelBins = 4096;
 constexpr int kSelHistGrid = 512;      // its work-groups (each clears and flushes a histogram)
 
 // The first histogram's level, then the refinements of a group too long to list.
-constexpr int kSelLevels = 3;
+constexpr int kSelLevels = 4;
 
 enum : int32_t { kSelDone = 0, kSelList = 1, kSelTie = 2, kSelWide = 3, kSelLast = 4 };
 
@@ -271,15 +271,16 @@ struct SelState {      // device scalars of one selection after a level
   int64_t need;        // rows of the group to take
   int64_t in;          // rows of the group
   uint64_t prefix;     // the bits above `shift` that the group's keys share
-  int64_t last;        // kSelTie: the last row taken
-  uint64_t least;      // kSelLast: smallest and largest key of the group
-  uint64_t most;
   int32_t shift;
   int32_t mode;        // kSelDone: the group is taken whole; kSelList: its rows are listed; kSelTie: they share
-                       // one key, counted per tile; kSelWide: their next digit is counted; kSelLast: both
-                       // listed and counted per tile
+                       // one key, counted per tile; kSelWide: their next digit is counted, and they are counted per
+                       // tile; kSelLast: both listed and counted per tile
   uint32_t listed;
   uint32_t pad;
+};
+
+struct SelRange {      // smallest and largest key of a work-group's rows of a group (least > most: none)
+  uint64_t least, most;
 };
 
 struct SelLaunch {
@@ -305,6 +306,7 @@ struct SelLaunch {
   int32_t* crows;
   uint32_t* tile_counts;    // [tiles]
   SelState* state;          // [kSelLevels]
+  SelRange* ranges;         // [kSelLevels][kSelGrid]: of the pass that counted or listed the level's group
   int grid;
 };
 

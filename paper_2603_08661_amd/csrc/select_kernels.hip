@@ -2,7 +2,7 @@
 // takes (the selection that feeds it; Sec. 2.1's edge scores moved to the
 // Gaussians, Sec. 3's gradient threshold and warm-up, and a budget).
 //
-//   sel_clear   : scores[0, N) = 0, the radix histograms and the key OR = 0
+//   sel_clear   : scores[0, N) = 0, the histograms and the lists' lengths = 0
 //                 (fill kernels, so the call can be captured)
 //   sel_scatter : per contribution (Gaussian g, view v, pixel p, weight w):
 //                 scores[g] += floor(fl32(E_v[p] * w) * 2^32); each
@@ -18,13 +18,13 @@
 //                 rows above the bin are selected, rows inside it listed (or,
 //                 where the bin is one exact key shared by more rows than are
 //                 still to take, counted per tile)
-//   sel_refine  : (twice) where that list would be long, because most scores
-//                 lie within 1.6% of each other, the next 12 bits are counted
-//                 instead, by all work-groups, and the rows of the K-th key's
-//                 digit listed (or counted on); nothing to do otherwise
+//   sel_refine  : (three times) where that list would be long, because most
+//                 scores lie within 1.6% of each other, the next 12 bits are
+//                 counted instead, by all work-groups, and the rows of the K-th
+//                 key's digit listed (or counted on); nothing to do otherwise
 //   sel_finish  : one work-group: exact selection among the listed keys, ties
-//                 by lower index; or the last row of a tie from the tile counts
-//   sel_ties    : the rows of such a tie (nothing to do otherwise)
+//                 by lower index; or all of them: the rows of one shared key, up
+//                 to the last one taken, found from the tile counts
 #include "igsp_internal.h"
 
 namespace igsp {
@@ -48,12 +48,9 @@ __global__ __launch_bounds__(kSelThreads) void sel_clear_kernel(SelLaunch S) {
   for (int64_t g = (int64_t)blockIdx.x * kSelThreads + threadIdx.x; g < N; g += (int64_t)gridDim.x * kSelThreads)
     S.scores[g] = 0;
   if (blockIdx.x == 0) {
-    for (int i = threadIdx.x; i < kSelLevels * kSelBins; i += kSelThreads) S.hist[i] = 0;
-    if (threadIdx.x < kSelLevels) {
-      S.state[threadIdx.x].listed = 0;
-      S.state[threadIdx.x].least = ~0ull;
-      S.state[threadIdx.x].most = 0;
-    }
+    for (int i = threadIdx.x; i < kSelLevels * kSelBins / 4; i += kSelThreads)
+      reinterpret_cast<uint4*>(S.hist)[i] = uint4{0u, 0u, 0u, 0u};
+    if (threadIdx.x < kSelLevels) S.state[threadIdx.x].listed = 0;
   }
 }
 
@@ -315,9 +312,7 @@ __device__ __forceinline__ SelPick pick_bin(const SelLaunch& S, const uint32_t* 
 
 // How the rest of a group of rows is selected: its keys share the bits above
 // `shift`, `need` of its `in` rows are taken. A list is finished by one
-// work-group, so a long one is refined first: 3M scores within 1%, 0.6M of
-// them taken, 7.4 ms with the list alone and 0.18 refined; all equal, 17.9 and
-// 0.29.
+// work-group, so a long one is refined first.
 constexpr int64_t kSelLongList = 8192;
 
 __device__ __forceinline__ int group_mode(int64_t need, int64_t in, int shift, int level) {
@@ -335,12 +330,50 @@ struct SelLds {
     uint32_t hist[kSelBins];
   };
   int32_t row[kSelTile];
+  SelRange range[kSelThreads / 64];
   uint32_t n, base;
 };
 static_assert(kSelBins * sizeof(uint32_t) <= kSelTile * sizeof(uint64_t), "the histogram fits the keys");
 
 constexpr int kSelDigit = 12;
 static_assert((1 << kSelDigit) == kSelBins, "a digit is a bin");
+
+// The smallest and the largest of the NT threads' keys, in every thread of the
+// work-group. (A work-group's range is stored, and all are read by every
+// work-group of the next launch, 16 KB at most: minima and maxima taken by
+// atomics on one address follow one another at about 11 ns.)
+template <int NT>
+__device__ __forceinline__ SelRange wg_range(SelRange r, SelRange* wave /* [NT / 64] */) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    const uint64_t a = (uint64_t)__shfl_xor((unsigned long long)r.least, o, 64);
+    const uint64_t b = (uint64_t)__shfl_xor((unsigned long long)r.most, o, 64);
+    r.least = a < r.least ? a : r.least;
+    r.most = b > r.most ? b : r.most;
+  }
+  if ((threadIdx.x & 63) == 0) wave[threadIdx.x >> 6] = r;
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < NT / 64; ++k) {
+    r.least = wave[k].least < r.least ? wave[k].least : r.least;
+    r.most = wave[k].most > r.most ? wave[k].most : r.most;
+  }
+  return r;
+}
+
+// The smallest and largest key of a level's group, from the work-groups of the
+// pass over its nt tiles.
+template <int NT>
+__device__ __forceinline__ SelRange group_range(const SelLaunch& S, int level, int64_t nt, SelRange* wave) {
+  SelRange r = {~0ull, 0ull};
+  const int n = nt < S.grid ? (int)nt : S.grid;
+  for (int i = threadIdx.x; i < n; i += NT) {
+    const SelRange q = S.ranges[level * kSelGrid + i];
+    r.least = q.least < r.least ? q.least : r.least;
+    r.most = q.most > r.most ? q.most : r.most;
+  }
+  return wg_range<NT>(r, wave);
+}
 
 // A pass over the rows: `above(key)` rows are selected (the mask is written
 // for every row, or only for those: WRITE), rows of the group (key >> shift ==
@@ -352,6 +385,7 @@ __device__ __forceinline__ void sel_pass(const SelLaunch& S, int64_t N, int leve
   const int64_t nt = (N + kSelTile - 1) / kSelTile;
   const int bits = shift < kSelDigit ? shift : kSelDigit;
   uint64_t least = ~0ull, most = 0;
+  const bool ranged = mode == kSelWide || mode == kSelLast, counted = ranged || mode == kSelTie;
   if (mode == kSelWide)
     for (int i = threadIdx.x; i < kSelBins; i += kSelThreads) l.hist[i] = 0;
   if (threadIdx.x == 0) l.n = 0;
@@ -366,22 +400,24 @@ __device__ __forceinline__ void sel_pass(const SelLaunch& S, int64_t N, int leve
       const bool up = key[k] && above(key[k]);
       if (g < N && (WRITE || up)) S.mask[g] = (uint8_t)up;
       if (mode == kSelDone || !key[k] || (key[k] >> shift) != prefix) continue;
-      if (mode == kSelTie || mode == kSelLast) ++ties;
+      ++ties;
+      if (ranged) {
+        least = key[k] < least ? key[k] : least;
+        most = key[k] > most ? key[k] : most;
+      }
       if (mode == kSelWide) atomicAdd(&l.hist[(uint32_t)(key[k] >> (shift - bits)) & ((1u << bits) - 1u)], 1u);
       if (mode == kSelList || mode == kSelLast) {
         const uint32_t at = atomicAdd(&l.n, 1u);
         l.key[at] = key[k];
         l.row[at] = (int32_t)g;
-        least = key[k] < least ? key[k] : least;
-        most = key[k] > most ? key[k] : most;
       }
     }
-    if (mode == kSelDone || mode == kSelWide) continue;  // uniform
-    if (mode == kSelTie || mode == kSelLast) {
+    if (mode == kSelDone) continue;  // uniform, here and below
+    if (counted) {
       uint32_t total = 0;
       (void)sel_scan(ties, wsum, total);
       if (threadIdx.x == 0) S.tile_counts[t] = total;
-      if (mode == kSelTie) continue;
+      if (mode != kSelLast) continue;
     }
     __syncthreads();
     if (threadIdx.x == 0 && l.n) l.base = atomicAdd(&st->listed, l.n);
@@ -402,18 +438,9 @@ __device__ __forceinline__ void sel_pass(const SelLaunch& S, int64_t N, int leve
       if (c) atomicAdd(&S.hist[(level + 1) * kSelBins + i], c);
     }
   }
-  if (mode == kSelLast) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-      const uint64_t a = (uint64_t)__shfl_xor((unsigned long long)least, o, 64);
-      const uint64_t b = (uint64_t)__shfl_xor((unsigned long long)most, o, 64);
-      least = a < least ? a : least;
-      most = b > most ? b : most;
-    }
-    if ((threadIdx.x & 63) == 0 && most) {
-      atomicMin(reinterpret_cast<unsigned long long*>(&st->least), (unsigned long long)least);
-      atomicMax(reinterpret_cast<unsigned long long*>(&st->most), (unsigned long long)most);
-    }
+  if (ranged) {
+    const SelRange r = wg_range<kSelThreads>(SelRange{least, most}, l.range);
+    if (threadIdx.x == 0) S.ranges[level * kSelGrid + blockIdx.x] = r;
   }
 }
 
@@ -444,7 +471,13 @@ __global__ __launch_bounds__(kSelThreads) void sel_collect_kernel(SelLaunch S) {
   sel_pass<true>(S, N, 0, mode, prefix, shift, l, wsum, [&](uint64_t key) { return key_bin(key) >= least; });
 }
 
-// The next digit of a group whose list would be long.
+// The next digit of a group whose list would be long. A group of one key is a
+// tie at once, and bits that all of a group's keys share are passed over, so
+// that equal scores and ones that differ in their last bits alone take one and
+// three passes. All work-groups take part: the selection by one of them (as
+// below) of 3M scores, all equal but for one that is 3 units larger, took 12.7 ms
+// a call where this takes 0.19; all equal, 286 and 156 us; within 1%, 7.4 ms and
+// 180 us (3M different scores: 155 us).
 __global__ __launch_bounds__(kSelThreads) void sel_refine_kernel(SelLaunch S, int level) {
   __shared__ uint32_t wsum[kSelThreads / 64];
   __shared__ SelPick s_pick;
@@ -461,10 +494,21 @@ __global__ __launch_bounds__(kSelThreads) void sel_refine_kernel(SelLaunch S, in
   const int64_t N = live_count(S);
   const int64_t nt = (N + kSelTile - 1) / kSelTile;
   if ((int64_t)blockIdx.x >= nt && blockIdx.x > 0) return;
+  const SelRange range = group_range<kSelThreads>(S, level - 1, nt, l.range);
+  if (range.least == range.most) {  // counted per tile by the pass before
+    if (blockIdx.x == 0 && threadIdx.x == 0) put_group(S.state + level, from->need, from->in, range.least, 0, kSelTie);
+    return;
+  }
   const uint64_t prefix0 = from->prefix;
-  const int shift0 = from->shift, bits = shift0 < kSelDigit ? shift0 : kSelDigit, shift = shift0 - bits;
+  const int shift0 = from->shift, bits = shift0 < kSelDigit ? shift0 : kSelDigit;
   const SelPick p = pick_bin(S, S.hist + level * kSelBins, N, from->need, wsum, &s_pick);
-  const uint64_t prefix = (prefix0 << bits) | (uint64_t)p.bin;
+  int shift = shift0 - bits;
+  uint64_t prefix = (prefix0 << bits) | (uint64_t)p.bin;
+  const int open = 64 - __clzll((long long)(range.least ^ range.most));  // bits in which the old group's keys differ
+  if (open < shift) {  // then the digit is one bin: the group is as it was
+    shift = open;
+    prefix = range.least >> open;
+  }
   const int mode = group_mode(p.need, p.in_bin, shift, level);
   if (blockIdx.x == 0 && threadIdx.x == 0) put_group(S.state + level, p.need, p.in_bin, prefix, shift, mode);
   const uint64_t least = mode == kSelDone ? prefix : prefix + 1;
@@ -472,7 +516,7 @@ __global__ __launch_bounds__(kSelThreads) void sel_refine_kernel(SelLaunch S, in
                   [&](uint64_t key) { return (key >> shift0) == prefix0 && (key >> shift) >= least; });
 }
 
-// One work-group of kFinThreads threads. A digit of kFinBits bits per pass.
+// Work-groups of kFinThreads threads; a list's digit of kFinBits bits per pass.
 constexpr int kFinThreads = 1024;
 constexpr int kFinBits = 11;
 constexpr int kFinBins = 1 << kFinBits;
@@ -526,30 +570,32 @@ __device__ __forceinline__ uint32_t fin_pass(uint32_t n, Match match, Digit digi
   return d;
 }
 
-// The rest of the selection, by one work-group. Bound by latency: a list is
-// the candidates of 1/64 of an octave of scores (about 5,000 for 1.2M of 3M
-// Gaussians), 2 passes of 2 us, or at most kSelLongList. (Longer only after
-// both refinements, where more rows than that agree in 30 bits and are still
-// not all equal: about 2.4 ms a pass for 3M rows.)
+// The rest of the selection. A list is one work-group's: the candidates of
+// 1/64 of an octave of scores (about 5,000 for 1.2M of 3M Gaussians), or at
+// most kSelLongList, bound by latency (4 to 10 us). It is longer only where
+// more rows than that agree in the 43 bits that the histogram and three digits
+// resolve (keys of 44 bits and more: scores of 2048 and above) and still differ;
+// then a pass over it takes about 0.8 ms for each million of its rows. The rows
+// of one key are taken by all work-groups, each of which finds the last one
+// from the tile counts (1,465 words for 3M rows).
+constexpr int kFinGrid = 256;
+
 __global__ __launch_bounds__(kFinThreads) void sel_finish_kernel(SelLaunch S) {
   __shared__ uint32_t h[kFinBins];
   __shared__ uint32_t wsum[kFinThreads / 64];
   __shared__ int64_t pick[3];
-  SelState* const st = S.state + kSelLevels - 1;
+  const SelState* const st = S.state + kSelLevels - 1;
   int mode = st->mode;
   int64_t need = st->need;
   uint64_t key = st->prefix;  // kSelTie: the one key
   if (mode == kSelLast) {
-    const bool one = st->least == st->most;
-    if (one) key = st->least;
-    mode = one ? kSelTie : kSelList;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      st->mode = mode;
-      st->prefix = key;
-    }
+    __shared__ SelRange wave[kFinThreads / 64];
+    const SelRange r = group_range<kFinThreads>(S, kSelLevels - 1, (live_count(S) + kSelTile - 1) / kSelTile, wave);
+    mode = r.least == r.most ? kSelTie : kSelList;
+    if (mode == kSelTie) key = r.least;
   }
   if (mode == kSelList) {
+    if (blockIdx.x > 0) return;
     const uint32_t n = st->listed;
     const uint64_t* keys = S.ckeys;
     const int32_t* rows = S.crows;
@@ -604,22 +650,17 @@ __global__ __launch_bounds__(kFinThreads) void sel_finish_kernel(SelLaunch S) {
       }
     }
     __syncthreads();
+    static_assert(kSelTile == 2 * kFinThreads, "two rows of the tile per thread");
     const int64_t g0 = pick[0] * kSelTile + 2 * threadIdx.x;
     const bool a = g0 < N && key_of(S, g0) == key, b = g0 + 1 < N && key_of(S, g0 + 1) == key;
     const int64_t r = (int64_t)fin_scan((a ? 1u : 0u) + (b ? 1u : 0u), wsum), want = pick[1];
-    if (a && r + 1 == want) st->last = g0;
-    if (b && r + (a ? 2 : 1) == want) st->last = g0 + 1;
+    if (a && r + 1 == want) pick[2] = g0;
+    if (b && r + (a ? 2 : 1) == want) pick[2] = g0 + 1;
+    __syncthreads();
+    const int64_t last = pick[2];
+    for (int64_t g = (int64_t)blockIdx.x * kFinThreads + threadIdx.x; g <= last; g += (int64_t)gridDim.x * kFinThreads)
+      if (key_of(S, g) == key) S.mask[g] = 1;
   }
-}
-
-// The tied rows up to the last one taken.
-__global__ __launch_bounds__(kSelThreads) void sel_ties_kernel(SelLaunch S) {
-  const SelState* const st = S.state + kSelLevels - 1;
-  if (st->mode != kSelTie) return;
-  const int64_t last = st->last;
-  const uint64_t key = st->prefix;
-  for (int64_t g = (int64_t)blockIdx.x * kSelThreads + threadIdx.x; g <= last; g += (int64_t)gridDim.x * kSelThreads)
-    if (key_of(S, g) == key) S.mask[g] = 1;
 }
 
 }  // namespace
@@ -666,8 +707,7 @@ hipError_t launch_select(const SelLaunch& S, hipStream_t s) {
   hipLaunchKernelGGL(sel_collect_kernel, dim3(grid), dim3(kSelThreads), 0, s, S);
   for (int level = 1; level < kSelLevels; ++level)
     hipLaunchKernelGGL(sel_refine_kernel, dim3(grid), dim3(kSelThreads), 0, s, S, level);
-  hipLaunchKernelGGL(sel_finish_kernel, dim3(1), dim3(kFinThreads), 0, s, S);
-  hipLaunchKernelGGL(sel_ties_kernel, dim3(grid), dim3(kSelThreads), 0, s, S);
+  hipLaunchKernelGGL(sel_finish_kernel, dim3(grid < kFinGrid ? grid : kFinGrid), dim3(kFinThreads), 0, s, S);
   return hipGetLastError();
 }
 

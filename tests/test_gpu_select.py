@@ -183,3 +183,75 @@ def test_split_mask_concentrated_scores(N, keys):
     top = int(((scores == scores.max()) & (grad >= 0.5)).sum())
     for K in sorted({1, top, min(top + 1, cand), cand // 3, cand // 2, cand - 1, cand}):
         run(N, N + 3, W, H, c, grad, 0.5, False, N + K, maps, off)
+
+
+@pytest.mark.parametrize("N", [20_000, 70_001])
+@pytest.mark.parametrize("keys", ["outliers", "nested", "nested_deep", "nested_deep_equal"])
+def test_split_mask_refined_to_the_last_bit(N, keys):
+    """Groups longer than a list whose refinement goes on: all scores equal but
+    for some a few units of 2^-32 larger (the shared bits are passed over); half
+    of them equal and others apart by every power of two, so that each digit
+    leaves equal and different keys, of 41 bits (resolved by three digits) and of
+    45 (two bits stay open, the last list is long; or its keys are all equal). K
+    falls on the edges of the equal scores and inside them."""
+    i = np.arange(N)
+    base = 256.0 if keys in ("outliers", "nested") else 4096.0
+    lowest = 2 if keys == "nested_deep_equal" else 0
+    top = 32 + int(np.log2(base))
+    first = np.full(N, base)
+    if keys == "outliers":
+        g2, w2 = i[i % 97 == 0], (1.0 + i[i % 97 == 0] % 3) * 2.0 ** -32
+    else:
+        first = np.where(i % 5 == 4, base * (1.0 + (i * 7919 % N) * (0.9 / N)), first)
+        g2 = i[i % 5 == 3]
+        w2 = 2.0 ** (lowest + g2 // 5 % (top - lowest) - 32)
+    W, H, off = [3], [3], np.zeros(1, np.int64)
+    maps = np.ones(9, np.float32)                           # E = 1 at the one pixel used
+    g, w = np.r_[i, g2].astype(np.int32), np.r_[first, w2].astype(np.float32)
+    c = synth.Contributions(g, np.zeros(g.size, np.int32), np.full(g.size, 4, np.int32), w)
+    grad = np.where(i % 11 == 0, 0.1, 1.0).astype(np.float32)
+    scores = oracle.split_scores(maps, W, H, off, c.gauss, c.view, c.pixel, c.weight, N)
+    cand = grad >= 0.5
+    equal = scores == int(base * 2 ** 32)
+    assert (equal & cand).sum() > 8192
+    above, upto = int((cand & (scores > scores[equal][0])).sum()), int((cand & (scores >= scores[equal][0])).sum())
+    for K in sorted({above - 1, above, above + 1, (above + upto) // 2, upto - 1, min(upto, int(cand.sum()))}):
+        run(N, N + 3, W, H, c, grad, 0.5, False, N + K, maps, off)
+
+
+@pytest.mark.parametrize("keys", ["equal", "outlier"])
+def test_split_mask_time_does_not_follow_the_scores(keys):
+    """A million scores that are all equal, or but for one a few units larger,
+    take no more than four times as long as a million different ones (before all
+    work-groups took part in the last digits: 46 times)."""
+    import torch
+
+    import paper_2603_08661_amd as igsp
+
+    dev, N = torch.device("cuda:0"), 1_000_000
+    gen = torch.Generator(device=dev).manual_seed(3)
+    gauss = torch.arange(N + 1, device=dev, dtype=torch.int32)
+    gauss[N] = N // 2
+    zero = torch.zeros(N + 1, dtype=torch.int32, device=dev)
+    maps, grad = torch.ones(9, device=dev), torch.ones(N, device=dev)
+    count = torch.tensor([N], dtype=torch.int64, device=dev)
+    mask, scores = torch.zeros(N, dtype=torch.uint8, device=dev), torch.zeros(N, dtype=torch.int64, device=dev)
+    spread = torch.rand(N + 1, generator=gen, device=dev).mul_(4.0).exp_()
+    alike = torch.full((N + 1,), 256.0, device=dev)
+    for w in (spread, alike):
+        w[N] = 3 * 2.0 ** -32 if keys == "outlier" else 0.0
+    took = []
+    for w in (spread, alike):
+        args = (maps, ([3], [3], [0], [0]), gauss, zero, zero, w, grad, count, mask, scores)
+        best = np.inf
+        for _ in range(5):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            for _ in range(4):
+                igsp.split_mask(*args, grad_threshold=0.5, budget=N + N // 5)
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b) / 4)
+        took.append(best)
+    print(f"spread {took[0] * 1e3:.0f} us, {keys} {took[1] * 1e3:.0f} us", flush=True)
+    assert took[1] < 4 * took[0], took
