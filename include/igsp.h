@@ -109,9 +109,9 @@ typedef struct {
   int32_t precision;     /* igsp_precision                                    */
   int32_t batched;       /* igsp_form                                         */
   int32_t seg_rows;      /* output rows per wavefront segment; 0 = tuned.
-                            Marched in whole rounds of six rows, and at 10
-                            rows in single rounds where the views are too
-                            few to fill the chip                              */
+                            Marched in whole rounds of six rows (rounded up),
+                            and at 10 rows in single rounds where the views
+                            are too few to fill the chip                      */
   int32_t wg_waves;      /* wavefronts per work-group (1, 2, 4, 8); 0 = tuned */
   float* medians;        /* (device, optional) [n_views]: the median surviving
                             magnitude of each view, in DN per pixel of an
@@ -182,9 +182,10 @@ igsp_status igsp_edge_autotune(const uint8_t* images, const igsp_view* views, in
  * the tallest of 64, 40, 28, 22, 16 rows that gives the stencil launch 16
  * wavefronts per CU, or 10 rows if none does; the plain form counts the
  * wavefronts of one view's launch, the batched forms those of all views).
- * Tuned entries
- * come from the file IGSP_TUNE_DEFAULTS names (the shipped table, read only)
- * and then IGSP_TUNE_CACHE (the autotuner's output), read once per process.
+ * seg_rows is the option's value, which can be passed back to the same effect;
+ * how it is marched stands at igsp_edge_opts. Tuned entries come from the file
+ * IGSP_TUNE_DEFAULTS names (the shipped table, read only) and then
+ * IGSP_TUNE_CACHE (the autotuner's output), read once per process.
  * opts (host, in/out). Touches no device memory and enqueues nothing.
  */
 igsp_status igsp_edge_resolve(const igsp_view* views, int32_t n_views, igsp_edge_opts* opts);

@@ -311,7 +311,8 @@ def edge_autotune(images, views, out_maps, precision="fp32", batched=True, strea
 
 
 def edge_resolve(views, precision="fp32", batched=True, seg_rows=0, wg_waves=0):
-    """(form name, seg_rows, wg_waves) that edge_importance would use."""
+    """(form name, seg_rows, wg_waves) that edge_importance would use, as its
+    options (a segment is marched in whole rounds of six rows)."""
     tab, n = view_table(*views)
     p = PRECISIONS[precision] if isinstance(precision, str) else int(precision)
     o = EdgeOpts(p, form_code(batched), int(seg_rows), int(wg_waves), None, None, None)

@@ -65,7 +65,7 @@ hipError_t upload(T** dptr, const std::vector<T>& v) {
 
 struct EdgeKey {
   int device;
-  int precision, seg_rows, wg_waves;
+  int precision, seg_rows, wg_waves;  // seg_rows: as marched
   std::vector<igsp_view> views;
   bool operator==(const EdgeKey& o) const {
     if (device != o.device || precision != o.precision || seg_rows != o.seg_rows || wg_waves != o.wg_waves ||
@@ -78,7 +78,6 @@ struct EdgeKey {
 struct EdgePlan {
   EdgeKey key;
   int n_views = 0;
-  int seg_rows = 0;  // rows per wavefront segment in the items (key.seg_rows, or less)
   ViewDesc* d_views = nullptr;
   EdgeItem* d_items = nullptr;
   EdgeItem* d_items_all = nullptr;  // the same items in the order of a launch over every view
@@ -130,50 +129,6 @@ int device_cus() {
   if (it != cache.end()) return it->second;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) return 256;
   return cache[dev] = cus;
-}
-
-// Segment height when none is given or tuned: the tallest of a few heights
-// that still gives a stencil launch 16 wavefronts per CU (four per SIMD),
-// else the shortest. A wavefront's march is a chain of dependent rows, so a
-// launch with fewer wavefronts than the chip holds lasts about one segment:
-// shorter segments then save more time than their extra halo rows cost. The
-// plain form launches each view on its own, so it counts per view.
-constexpr int kShortestSeg = 10;
-
-// Wavefronts of a stencil launch over the views at a segment height.
-int64_t stencil_waves(const igsp_view* views, int32_t n, int seg) {
-  int64_t waves = 0;
-  for (int i = 0; i < n; ++i)
-    waves += (int64_t)((views[i].width + kStripCols - 1) / kStripCols) * ((views[i].height + seg - 1) / seg);
-  return waves;
-}
-
-int default_seg_rows(const igsp_view* views, int32_t n, int form) {
-  static const int kHeights[] = {64, 40, 28, 22, 16, kShortestSeg};
-  const int64_t target = 16 * (int64_t)device_cus();
-  for (int seg : kHeights) {
-    int64_t waves = stencil_waves(views, n, seg);
-    if (form == IGSP_PLAIN && n > 0) waves /= n;
-    if (waves >= target) return seg;
-  }
-  return kShortestSeg;
-}
-
-// Rows per segment as a plan marches them: whole rounds of the stencil loop's
-// six rows (the rows past a segment's end would be computed all the same;
-// 150 views BF16, 100 rows marched as 102: 864 -> 855 us of edge maps). A plan
-// of the shortest segments whose wavefronts would leave most SIMDs with one
-// or none splits them once more, to one round: a lone wavefront takes about
-// 0.5 us a row, and shorter segments save more than their window-filling rows
-// (2.7 rows' work) and histogram flushes cost. At 10 rows marched as 12 / 6:
-// one FP32 256x192 view (64 wavefronts at 6 rows) 22.8 / 19.9 us, 1297x840
-// (840) 29.4 / 28.1, 1600x1067 (1246) 34.7 / 34.4, two 1297x840 (1680) 37.4 /
-// 37.6: the line is at 1.5 wavefronts per SIMD.
-constexpr int kRound = 6;
-
-int plan_seg_rows(const igsp_view* views, int32_t n, int seg) {
-  if (seg == kShortestSeg && stencil_waves(views, n, kRound) <= 6 * (int64_t)device_cus()) return kRound;
-  return (seg + kRound - 1) / kRound * kRound;
 }
 
 // ------------------------------------------------------------------ tuning
@@ -290,8 +245,7 @@ igsp_status build_edge_plan(const EdgeKey& key, std::shared_ptr<EdgePlan>* out) 
   plan->key = key;
   const int n = (int)key.views.size();
   plan->n_views = n;
-  plan->seg_rows = plan_seg_rows(key.views.data(), n, key.seg_rows);
-  const int band = plan->seg_rows * key.wg_waves;
+  const int band = key.seg_rows * key.wg_waves;
   const int esz = key.precision == IGSP_FP32 ? 4 : 2;
   std::vector<ViewDesc> vd(n);
   std::vector<EdgeItem> items;
@@ -482,8 +436,8 @@ igsp_status get_edge_plan(const igsp_view* views, int32_t n_views, const igsp_ed
   EdgeKey key;
   key.device = dev;
   key.precision = opts ? opts->precision : IGSP_FP32;
-  const int form = resolve_form(views, n_views, opts);
-  int seg = default_seg_rows(views, n_views, form), wgw = default_wg_waves();
+  const int form = resolve_form(views, n_views, opts), cus = device_cus();
+  int seg = default_seg_rows(views, n_views, form, cus), wgw = default_wg_waves();
   if (!opts || (opts->seg_rows == 0 && opts->wg_waves == 0)) {
     load_tune_cache();
     auto it = g_tuned.find(tune_key(views, n_views, key.precision, opts ? opts->batched : IGSP_BATCHED));
@@ -492,7 +446,7 @@ igsp_status get_edge_plan(const igsp_view* views, int32_t n_views, const igsp_ed
       wgw = it->second.wg_waves;
     }
   }
-  key.seg_rows = (opts && opts->seg_rows) ? opts->seg_rows : seg;
+  key.seg_rows = marched_rows(views, n_views, (opts && opts->seg_rows) ? opts->seg_rows : seg, cus);
   key.wg_waves = (opts && opts->wg_waves) ? opts->wg_waves : wgw;
   key.views.assign(views, views + n_views);
   auto extras = [form](EdgePlan* P) -> igsp_status {
@@ -561,7 +515,7 @@ igsp_status enqueue_edge(EdgePlan* P, const uint8_t* images, int64_t img_end, fl
   L.status = opts ? opts->status : nullptr;
   L.precision = P->key.precision;
   L.wg_waves = P->key.wg_waves;
-  L.seg_rows = P->seg_rows;
+  L.seg_rows = P->key.seg_rows;
   const int form = resolve_form(P->key.views.data(), P->n_views, opts);
   const bool batched = form != IGSP_PLAIN;
   const int n = P->n_views;
@@ -940,7 +894,7 @@ extern "C" igsp_status igsp_edge_resolve(const igsp_view* views, int32_t n_views
   if (opts->batched < IGSP_PLAIN || opts->batched > IGSP_UNFUSED) return IGSP_ERR_PARAM;
   std::lock_guard<std::mutex> lk(g_mu);
   const int form = resolve_form(views, n_views, opts);
-  int seg = default_seg_rows(views, n_views, form), wgw = default_wg_waves();
+  int seg = default_seg_rows(views, n_views, form, device_cus()), wgw = default_wg_waves();
   if (opts->seg_rows == 0 && opts->wg_waves == 0) {
     load_tune_cache();
     auto it = g_tuned.find(tune_key(views, n_views, opts->precision, opts->batched));
@@ -1022,7 +976,7 @@ extern "C" igsp_status igsp_edge_autotune(const uint8_t* images, const igsp_view
       st = time_candidate(cands[k], 16, &ms);
       cands[k].ms = std::min<double>(cands[k].ms, ms);
     }
-  TuneVal bestv{default_seg_rows(views, n_views, forms.back()), default_wg_waves(), forms.back(), 1e30};
+  TuneVal bestv{default_seg_rows(views, n_views, forms.back(), device_cus()), default_wg_waves(), forms.back(), 1e30};
   for (size_t k = 0; k < top; ++k)
     if (cands[k].ms < bestv.ms) bestv = cands[k];
   (void)hipEventDestroy(e0);

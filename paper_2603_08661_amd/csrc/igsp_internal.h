@@ -8,18 +8,11 @@
 #include <hip/hip_runtime.h>
 
 #include "../../include/igsp.h"
+#include "schedule.h"
 
 namespace igsp {
 
 // ---------------------------------------------------------------- edge path
-
-// Strip geometry of the fused stencil kernel: a wavefront owns 64 lanes x 4
-// adjacent columns = 256 input columns, of which the 4 outermost on each
-// side are halo (2 blur + 1 Sobel + 1 suppression), leaving 248 outputs.
-constexpr int kLanePx = 4;
-constexpr int kWaveCols = 64 * kLanePx;       // 256
-constexpr int kHalo = 4;
-constexpr int kStripCols = kWaveCols - 2 * kHalo;  // 248
 
 // What the stencil pass stores for a surviving pixel, from the exact squared
 // unnormalised Sobel magnitude M (1 <= M < 2^57 for 8-bit input):

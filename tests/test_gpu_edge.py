@@ -320,3 +320,29 @@ def test_fp32_short_chain_equal_and_distinct_values(n_views):
     b, mb, nb = gpu_edge(vb, "fp32", "unfused")
     assert np.array_equal(a, b) and np.array_equal(ma, mb) and np.array_equal(na, nb) and (na > 0).any()
     assert np.array_equal(p, b) and np.array_equal(mp, mb) and np.array_equal(np_, nb)
+
+
+def test_heights_marched_alike_share_a_plan():
+    """Segment heights of 8 to 12 rows are all marched as two rounds of six (this
+    view fills more than 1.5 wavefronts per SIMD at six rows, so 10 is too): one
+    plan, with one intermediate map, serves them. 13 rows take another."""
+    import torch
+
+    import paper_2603_08661_amd as igsp
+
+    W, H = 2000, 1500
+    dev = torch.device("cuda:0")
+    img = torch.from_numpy(np.concatenate([synth.image(63, W, H, 30, True).reshape(-1), np.zeros(16, np.uint8)])).to(dev)
+    views = ([W], [H], [0], [0])
+    maps = {seg: torch.zeros(W * H, device=dev) for seg in (12, 8, 9, 10, 11, 13)}
+    torch.cuda.synchronize()
+    igsp.release_plans()
+    free = {}
+    for seg, out in maps.items():      # (no torch operation in between: they allocate too)
+        igsp.edge_importance(img, views, out, precision="fp32", batched="staged", seg_rows=seg)
+        torch.cuda.synchronize()
+        free[seg] = torch.cuda.mem_get_info(dev)[0]
+    assert free[8] == free[9] == free[10] == free[11] == free[12], free
+    assert free[12] - free[13] >= 4 * W * H, free
+    assert all(torch.equal(m, maps[12]) for m in maps.values())
+    igsp.release_plans()
