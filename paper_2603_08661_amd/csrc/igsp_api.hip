@@ -446,7 +446,7 @@ igsp_status get_edge_plan(const igsp_view* views, int32_t n_views, const igsp_ed
       wgw = it->second.wg_waves;
     }
   }
-  key.seg_rows = marched_rows(views, n_views, (opts && opts->seg_rows) ? opts->seg_rows : seg, cus);
+  key.seg_rows = marched_rows(views, n_views, (opts && opts->seg_rows) ? opts->seg_rows : seg, form, cus);
   key.wg_waves = (opts && opts->wg_waves) ? opts->wg_waves : wgw;
   key.views.assign(views, views + n_views);
   auto extras = [form](EdgePlan* P) -> igsp_status {
