@@ -638,7 +638,7 @@ __device__ __forceinline__ void wave_strip(const EdgeLaunch& L, const ViewDesc& 
   else march<PREC, false, CPOL>(C, hist);
 }
 
-// This item's share of clearing its view's counts of the short chain, an equal
+// This item's share of clearing its view's counts of the short chains, an equal
 // part for each of the view's items.
 __device__ __forceinline__ void clear_fine_share(const EdgeLaunch& L, const ViewDesc& vd, const EdgeItem& it, int band,
                                                  int threads) {
@@ -659,13 +659,16 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(IGSP_FU
   const EdgeItem it = L.items[item];
   const ViewDesc vd = L.views[it.view];
   for (int i = threadIdx.x; i < NB / 4; i += NW * 64) reinterpret_cast<u32x4*>(hist)[i] = u32x4{0u, 0u, 0u, 0u};
-  // the short chain's counts start from zero (the long chain's selection
+  // the short chains' counts start from zero (the long chain's selection
   // launch clears them itself)
-  if (L.short_chain && it.x0 == 0 && it.y0 == 0) {
-    for (int i = threadIdx.x; i < kRefineBins; i += NW * 64) L.rhist[(int64_t)it.view * kRefineBins + i] = 0;
+  if (L.chain && it.x0 == 0 && it.y0 == 0) {
+    for (int i = threadIdx.x; i < kRefineBins; i += NW * 64) {
+      L.rhist[(int64_t)it.view * kRefineBins + i] = 0;
+      if (PREC == IGSP_FP32) L.rhist[((int64_t)L.n_views + it.view) * kRefineBins + i] = 0;
+    }
   }
   if constexpr (PREC == IGSP_FP32) {
-    if (L.short_chain) clear_fine_share(L, vd, it, L.seg_rows * NW, NW * 64);
+    if (L.chain) clear_fine_share(L, vd, it, L.seg_rows * NW, NW * 64);
   }
   __syncthreads();
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -756,7 +759,7 @@ __global__ __launch_bounds__(256) void median_select_kernel(EdgeLaunch L, int v0
   const uint32_t k = n ? (n - 1) / 2 : 0;
   if (n == 0) {
     if (threadIdx.x == 0) {
-      MedState st = {0u, 0, 0u, 0u, 0.0f, {0u, 0u, 0u}};
+      MedState st = {0u, 0, 0u, 0u, 0.0f, 0u, {0u, 0u}};
       finish_view(L, v, st);
       L.state[v] = st;
     }
@@ -768,7 +771,7 @@ __global__ __launch_bounds__(256) void median_select_kernel(EdgeLaunch L, int v0
       if (cum + c[j] > k) { b = b0 + j; break; }
       cum += c[j];
     }
-    MedState st = {Keys<PREC>::lo + (uint32_t)b, 16, k - cum, n, 0.0f, {0u, 0u, 0u}};
+    MedState st = {Keys<PREC>::lo + (uint32_t)b, 16, k - cum, n, 0.0f, 0u, {0u, 0u}};
     if (16 == final_shift(PREC)) finish_view(L, v, st);
     L.state[v] = st;
   }
@@ -993,6 +996,16 @@ __device__ __forceinline__ void refine_slots(const EdgeLaunch& L, const ViewDesc
   }
 }
 
+// The guarded chain's choice for a view, alike in every work-group: whether its
+// bucket holds more survivors than median_gather counts one by one, on average
+// per chunk (photographs: about 10 of 4 Ki pixels).
+constexpr uint32_t kGatherMany = 128;
+
+__device__ __forceinline__ bool many_values(const EdgeLaunch& L, const ViewDesc& vd, const MedState& st) {
+  const int64_t chunks = ((int64_t)strips_of(vd) * vd.H + kChunkSlots - 1) / kChunkSlots;
+  return L.chain == kChainGuarded && (int64_t)st.in > kGatherMany * chunks;
+}
+
 // Refinement pass `pass` over a row chunk: the state after `pass` steps
 // comes from the previous pass's histogram (each work-group takes that
 // step itself; the view's first chunk stores it for the next launch), then
@@ -1013,12 +1026,13 @@ __global__ __launch_bounds__(256) void median_refine_kernel(EdgeLaunch L, int ch
   const RowChunk ck = L.chunks[chunk0 + at];
   const int v = ck.view;
   const int64_t n = L.n_views;
+  const ViewDesc vd = L.views[v];
   MedState st = L.state[v];
+  if (L.chain == kChainGuarded && !many_values(L, vd, st)) return;  // counted by median_gather
   if (pass > 0) {
     st = refine_step(L, L.state[(pass - 1) * n + v], L.rhist + ((pass - 1) * n + v) * kRefineBins, DB, tmp, &s_st);
     if (ck.u0 == 0 && threadIdx.x == 0) L.state[pass * n + v] = st;
   }
-  const ViewDesc vd = L.views[v];
   hs[threadIdx.x] = 0;
   __syncthreads();
   const int lane = __lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1067,7 +1081,7 @@ __global__ __launch_bounds__(256) void median_refine_kernel(EdgeLaunch L, int ch
 // The state a previous launch left, through the scalar cache.
 __device__ __forceinline__ MedState load_uniform(const MedState* s) {
   cptr<uint32_t> p = as_constant(reinterpret_cast<const uint32_t*>(s));
-  return MedState{p[0], (int32_t)p[1], p[2], p[3], __uint_as_float(p[4]), {0u, 0u, 0u}};
+  return MedState{p[0], (int32_t)p[1], p[2], p[3], __uint_as_float(p[4]), p[5], {0u, 0u}};
 }
 
 // FP16's only refinement step from its 8 digit counts: few enough that every
@@ -1094,20 +1108,23 @@ __device__ __forceinline__ MedState refine_step8(const MedState& st, cptr<uint32
   return r;
 }
 
-// ---- the short chain (FP32 and FP16, launches of few chunks): every launch
-// costs its start, its end and one memory latency after another, whatever
-// its size, so the median takes one launch between the stencil and the
-// normalisation instead of three. median_gather selects the median's bucket
-// from the first histogram in every work-group (29 KB from L2) and counts
-// the survivors inside it by the bits that it leaves open; the normalisation's
-// work-groups finish the selection from those counts, and its first chunk of a view
-// clears the histogram. A 256x192 FP32 view's edge maps: 35.9 us with five
-// launches, 25.0 with these three (19.7 with its segments split and their
-// first rows made cheap); 1297x840: 40.7 and 32.0 (24.9). Latency-bound: the
+// ---- the short chains (FP32 and FP16, launches of few chunks: median_chain):
+// every launch costs its start, its end and one memory latency after another,
+// whatever its size, so the median takes one launch between the stencil and the
+// normalisation instead of FP16's two and FP32's three. median_gather selects the
+// median's bucket from the first histogram in every work-group (29 KB from L2) and
+// counts the survivors inside it by the bits that it leaves open; the
+// normalisation's work-groups finish the selection from those counts, and its
+// first chunk of a view clears the histogram. A 256x192 FP32 view's edge maps: 35.9
+// us with five launches, 25.0 with these three (19.7 with its segments split and
+// their first rows made cheap); 1297x840: 40.7 and 32.0 (24.9). Latency-bound: the
 // stencil's lone wavefronts take 9-13 us, the other two launches 5-8 us each.
-// Sums of
-// the histogram over whole binades, for median_gather to read instead of its
-// 7424 bins, cost the stencil more than they saved: every work-group adds to
+// The guarded chain (FP32): where a view's bucket holds many survivors,
+// median_gather counts the upper 8 of the 16 open bits alone, and a refinement
+// launch counts the lower 8. 1984x1376, stripes with noise: 454,000 additions of
+// one value each before, 61.0 -> 51.3 us; a photograph pays the launch, 32.8 -> 34.5.
+// Sums of the histogram over whole binades, for median_gather to read instead of
+// its 7424 bins, cost the stencil more than they saved: every work-group adds to
 // the same few words (1297x840: 28.4 -> 69.4 us).
 
 // The state after the first histogram, taken by a whole work-group (bins: its
@@ -1135,16 +1152,16 @@ __device__ __forceinline__ MedState select_first(const EdgeLaunch& L, int v, uin
   const uint32_t excl = block_excl_scan(sum, tmp, n);
   const uint32_t k = n ? (n - 1) / 2 : 0;
   if (n == 0) {
-    if (threadIdx.x == 0) *s_st = MedState{0u, 0, 0u, 0u, 0.0f, {0u, 0u, 0u}};
+    if (threadIdx.x == 0) *s_st = MedState{0u, 0, 0u, 0u, 0.0f, 0u, {0u, 0u}};
   } else if (excl <= k && k < excl + sum) {
-    uint32_t cum = excl;
+    uint32_t cum = excl, in = 0;
     int b = 0;
 #pragma unroll
     for (int j = 0; j < PER; ++j) {
-      if (cum + c[j] > k) { b = j; break; }
+      if (cum + c[j] > k) { b = j; in = c[j]; break; }
       cum += c[j];
     }
-    *s_st = MedState{Keys<PREC>::lo + (uint32_t)(threadIdx.x * PER + b), 16, k - cum, n, 0.0f, {0u, 0u, 0u}};
+    *s_st = MedState{Keys<PREC>::lo + (uint32_t)(threadIdx.x * PER + b), 16, k - cum, n, 0.0f, in, {0u, 0u}};
   }
   __syncthreads();
   return *s_st;
@@ -1220,6 +1237,14 @@ __global__ __launch_bounds__(256) void median_gather_kernel(EdgeLaunch L, int ch
       }
     }
   };
+  if (many_values(L, vd, st)) {  // the next digit alone; the refinement pass counts the last
+    lds[threadIdx.x] = 0;
+    __syncthreads();
+    each_candidate([&](uint32_t low) { atomicAdd(&lds[low >> 8], 1u); });
+    __syncthreads();
+    if (lds[threadIdx.x]) atomicAdd(coarse + threadIdx.x, lds[threadIdx.x]);
+    return;
+  }
   if (threadIdx.x == 0) cn = 0;
   __syncthreads();
   each_candidate([&](uint32_t low) {
@@ -1363,8 +1388,8 @@ __device__ __forceinline__ void norm_slots(const EdgeLaunch& L, const ViewDesc& 
 // Normalisation of a row chunk (of at most kChunkSlots slots: one walk step
 // per wavefront, loaded before the median is known). Each work-group takes
 // the last selection step itself, from the last pass's digit counts (in the
-// short chain FP32's last two), and the view's first
-// chunk stores the final state and writes the view's outputs.
+// short chains FP32's last two, where median_gather counted them), and the view's
+// first chunk stores the final state and writes the view's outputs.
 template <int PREC, bool SHORT>
 __global__ __launch_bounds__(256) void normalise_kernel(EdgeLaunch L, int chunk0) {
   __shared__ uint32_t tmp[4];
@@ -1384,7 +1409,7 @@ __global__ __launch_bounds__(256) void normalise_kernel(EdgeLaunch L, int chunk0
   } else {
     if constexpr (PREC == IGSP_FP16) {
       st = refine_step8(load_uniform(L.state + v), as_constant(L.rhist + v * (int64_t)kRefineBins));
-    } else if constexpr (SHORT) {
+    } else if (SHORT && !many_values(L, vd, load_uniform(L.state + v))) {
       st = resolve_view(L, v, load_uniform(L.state + v), tmp, &s_st);
     } else {
       st = refine_step(L, load_uniform(L.state + (P - 1) * n + v), L.rhist + ((P - 1) * n + v) * kRefineBins,
@@ -1672,7 +1697,7 @@ __device__ void select_hist(const EdgeLaunch& L, int v, uint32_t* tmp) {
   const uint32_t k = n ? (n - 1) / 2 : 0;
   if (n == 0) {
     if (threadIdx.x == 0) {
-      MedState st = {0u, 0, 0u, 0u, 0.0f, {0u, 0u, 0u}};
+      MedState st = {0u, 0, 0u, 0u, 0.0f, 0u, {0u, 0u}};
       finish_view(L, v, st);
       store_state(L.state + v, st);
     }
@@ -1687,7 +1712,7 @@ __device__ void select_hist(const EdgeLaunch& L, int v, uint32_t* tmp) {
       }
       cum += c;
     }
-    MedState st = {Keys<PREC>::lo + (uint32_t)b, 16, k - cum, n, 0.0f, {0u, 0u, 0u}};
+    MedState st = {Keys<PREC>::lo + (uint32_t)b, 16, k - cum, n, 0.0f, 0u, {0u, 0u}};
     if (16 == final_shift(PREC)) finish_view(L, v, st);
     store_state(L.state + v, st);
   }
@@ -1972,12 +1997,12 @@ hipError_t launch_normalise(const EdgeLaunch& L, int chunk0, int n_chunks, hipSt
   const dim3 g(n_chunks), b(256);
   switch (L.precision) {
     case IGSP_FP16:
-      if (L.short_chain) hipLaunchKernelGGL((normalise_kernel<IGSP_FP16, true>), g, b, 0, s, L, chunk0);
+      if (L.chain) hipLaunchKernelGGL((normalise_kernel<IGSP_FP16, true>), g, b, 0, s, L, chunk0);
       else hipLaunchKernelGGL((normalise_kernel<IGSP_FP16, false>), g, b, 0, s, L, chunk0);
       break;
     case IGSP_BF16: hipLaunchKernelGGL((normalise_kernel<IGSP_BF16, false>), g, b, 0, s, L, chunk0); break;
     default:
-      if (L.short_chain) hipLaunchKernelGGL((normalise_kernel<IGSP_FP32, true>), g, b, 0, s, L, chunk0);
+      if (L.chain) hipLaunchKernelGGL((normalise_kernel<IGSP_FP32, true>), g, b, 0, s, L, chunk0);
       else hipLaunchKernelGGL((normalise_kernel<IGSP_FP32, false>), g, b, 0, s, L, chunk0);
       break;
   }

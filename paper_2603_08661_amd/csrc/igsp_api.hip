@@ -87,7 +87,7 @@ struct EdgePlan {
   int n_wide = 0;
   uint32_t* d_cand = nullptr;     // FP32: median candidates and their counts per view
   uint32_t* d_cand_n = nullptr;
-  uint32_t* d_fine = nullptr;     // FP32: the short chain's counts, of at most kFineViews views
+  uint32_t* d_fine = nullptr;     // FP32: the short chains' counts, of at most kFineViews views
   std::vector<int> item_begin, chunk_begin, rchunk_begin;  // per view, size n_views + 1
   void* d_map = nullptr;
   uint32_t* d_hist = nullptr;
@@ -466,28 +466,6 @@ igsp_status get_edge_plan(const igsp_view* views, int32_t n_views, const igsp_ed
   return st;
 }
 
-// Whether the stages of views [v0, v1) take the short median chain (FP32,
-// FP16). It saves two (FP32) launches of 4 us, but every work-group then
-// selects from its view's whole first histogram: about 3 ns a chunk and 1/80
-// ns more for each chunk of the same view, against 8 us saved; FP16 costs and
-// saves half. Short against long, FP32: one 1297x840 view (293 chunks) 25.6
-// and 33.1 us, two 31.0 and 40.0, four (1180) 38.0 and 45.6, one 1984x1376
-// (688) 35.3 and 43.7, one 2473x1643 (929) 41.5 and 48.1, 64 views of 300x187
-// (1491) 42.7 and 45.7; FP16: 23.9 and 25.0, 28.1 and 29.8, 35.2 and 37.6,
-// 33.9 and 32.6, 42.8 and 39.1, 37.1 and 39.2, 200 of 300x187 77.6 and 72.7.
-// (FP32 alone would gain a little above the line too; a view whose stripes
-// have thousands of different magnitudes in one bucket, the worst for the
-// short chain's counts, does not: 1984x1376 62 and 54.)
-bool short_chain(const EdgePlan& P, int v0, int v1) {
-  if (P.key.precision == IGSP_FP32 && (v1 - v0 > kFineViews || !P.d_fine)) return false;
-  int64_t cost = 0;
-  for (int v = v0; v < v1 && cost <= 80 * 8000; ++v) {
-    const int64_t c = P.chunk_begin[v + 1] - P.chunk_begin[v];
-    cost += c * (80 * 3 + c);
-  }
-  return cost <= 80 * 8000;
-}
-
 igsp_status enqueue_edge(EdgePlan* P, const uint8_t* images, int64_t img_end, float* out_maps,
                          const igsp_edge_opts* opts, hipStream_t s) {
   EdgeLaunch L;
@@ -507,7 +485,7 @@ igsp_status enqueue_edge(EdgePlan* P, const uint8_t* images, int64_t img_end, fl
   L.view0 = 0;
   L.use_cand = 0;
   L.refine_slots = kRefineChunkSlots;
-  L.short_chain = 0;
+  L.chain = kChainLong;
   L.n_views = P->n_views;
   L.medians_dn = opts ? opts->medians : nullptr;
   L.survivors = opts ? opts->survivors : nullptr;
@@ -524,14 +502,20 @@ igsp_status enqueue_edge(EdgePlan* P, const uint8_t* images, int64_t img_end, fl
   const int passes = L.precision == IGSP_FP16 ? 1 : (L.precision == IGSP_FP32 ? 2 : 0);
   hipEvent_t* ev = L.stage_events;
   auto mark = [&](int k, hipStream_t st) -> hipError_t { return ev ? hipEventRecord(ev[k], st) : hipSuccess; };
-  auto is_short = [&](int v0, int v1) { return form != IGSP_UNFUSED && passes > 0 && short_chain(*P, v0, v1); };
+  auto chain = [&](int v0, int v1) {
+    return form == IGSP_UNFUSED ? (int)kChainLong : median_chain(L.precision, P->key.views.data() + v0, v1 - v0);
+  };
   // median selection (+ refinement passes) of views [v0, v1); the last
   // selection step is taken by the normalisation
   auto tail = [&](int v0, int v1, hipStream_t st) -> hipError_t {
-    if (is_short(v0, v1)) {
+    if (const int c = chain(v0, v1)) {
       EdgeLaunch LA = L;
+      LA.chain = c;
       LA.view0 = v0;
-      return launch_median_gather(LA, P->chunk_begin[v0], P->chunk_begin[v1] - P->chunk_begin[v0], st);
+      hipError_t e = launch_median_gather(LA, P->chunk_begin[v0], P->chunk_begin[v1] - P->chunk_begin[v0], st);
+      if (e != hipSuccess || c != kChainGuarded) return e;
+      LA.chunks = P->d_rchunks;
+      return launch_median_refine(LA, P->rchunk_begin[v0], P->rchunk_begin[v1] - P->rchunk_begin[v0], 1, st);
     }
     const bool wide = P->n_wide > 0 && v0 == 0 && v1 == n;
     const int f0 = wide ? 0 : P->rchunk_begin[v0], f1 = wide ? P->n_wide : P->rchunk_begin[v1];
@@ -549,14 +533,14 @@ igsp_status enqueue_edge(EdgePlan* P, const uint8_t* images, int64_t img_end, fl
   };
   auto stencil = [&](int v0, int v1, hipStream_t st) -> hipError_t {
     EdgeLaunch LA = L;
-    LA.short_chain = is_short(v0, v1);
+    LA.chain = chain(v0, v1);
     LA.view0 = v0;
     if (v0 == 0 && v1 == n) LA.items = P->d_items_all;
     return launch_edge_fused(LA, P->item_begin[v0], P->item_begin[v1] - P->item_begin[v0], st);
   };
   auto norm = [&](int v0, int v1, hipStream_t st) -> hipError_t {
     EdgeLaunch LA = L;
-    LA.short_chain = is_short(v0, v1);
+    LA.chain = chain(v0, v1);
     LA.view0 = v0;
     return launch_normalise(LA, P->chunk_begin[v0], P->chunk_begin[v1] - P->chunk_begin[v0], st);
   };

@@ -39,15 +39,9 @@ constexpr int kRefineBins = 256;          // radix digit of the refine passes
 constexpr int kRefineChunkSlots = 64;
 constexpr int kRefineWideSlots = 128;
 constexpr int64_t kWideSlots = 40000;
-// FP32's short median chain: counts of the 16 bits that the first histogram
-// leaves open (256 KiB a view), and the most views of a launch that takes it
-// (16 MiB of counts to clear, about 3 us).
+// FP32's short median chains: counts of the 16 bits that the first histogram
+// leaves open (256 KiB a view).
 constexpr int kFineBins = 1 << 16;
-constexpr int kFineViews = 64;
-// Slots (248 pixels each) per work-group of the other element-wise passes,
-// about 4 Ki pixels (measured best for normalisation).
-constexpr int kChunkSlots = 16;
-
 // The stored intermediate of a view is kept strip by strip: strip s (output
 // columns 248 s .. 248 s + 247) holds its rows one after another in slots of
 // 256 values (its 248 outputs and 8 unused values: one aligned 512-byte or
@@ -91,7 +85,8 @@ struct MedState {    // radix-select state of one view's median
   uint32_t rank;     // rank of the median inside the resolved bucket
   uint32_t n;        // survivors
   float med;         // median, stored units (valid once shift == final)
-  uint32_t pad[3];
+  uint32_t in;       // survivors in the first histogram's bucket (short chains)
+  uint32_t pad[2];
 };
 
 struct EdgeLaunch {
@@ -109,9 +104,9 @@ struct EdgeLaunch {
   uint32_t* cand_n;          // [n_views]: candidates found (more than the room: list not used)
   int refine_slots;          // slots per chunk of this refinement launch
   int use_cand;              // the refinement passes of this launch use the candidate lists
-  uint32_t* fine;            // FP32, short chain: [views of the launch][kFineBins] counts of the open 16 bits
-  int view0;                 // first view of the launch (short chain)
-  int short_chain;           // the median takes one launch (median_gather) before the normalisation
+  uint32_t* fine;            // FP32, short chains: [views of the launch][kFineBins] counts of the open 16 bits
+  int view0;                 // first view of the launch (short chains)
+  int chain;                 // kChainLong, kChainShort, kChainGuarded
   float* medians_dn;         // optional outputs
   int32_t* survivors;
   hipEvent_t* stage_events;  // optional, 4 events
@@ -190,7 +185,8 @@ struct UfLaunch {
 hipError_t launch_edge_fused(const EdgeLaunch& L, int item0, int n_items, hipStream_t s);
 hipError_t launch_median_select(const EdgeLaunch& L, int v0, int nv, hipStream_t s);
 hipError_t launch_median_refine(const EdgeLaunch& L, int chunk0, int n_chunks, int pass, hipStream_t s);
-// the short chain's only launch between the stencil and the normalisation
+// the short chains' first launch (kChainShort: the only one) between the stencil
+// and the normalisation
 hipError_t launch_median_gather(const EdgeLaunch& L, int chunk0, int n_chunks, hipStream_t s);
 hipError_t launch_normalise(const EdgeLaunch& L, int chunk0, int n_chunks, hipStream_t s);
 // The stencil steps of the unfused form: gray, blur, Sobel, suppression

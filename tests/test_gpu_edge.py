@@ -346,3 +346,58 @@ def test_heights_marched_alike_share_a_plan():
     assert free[12] - free[13] >= 4 * W * H, free
     assert all(torch.equal(m, maps[12]) for m in maps.values())
     igsp.release_plans()
+
+
+def _striped(w, h, rng=None):
+    """6-pixel stripes of one contrast, with a grey level of sensor noise."""
+    im = np.zeros((h, w, 3)) + ((((np.arange(w) // 3) % 2) * 180) + 30)[None, :, None]
+    if rng is not None:
+        im = im + rng.normal(0, 1.0, (h, w, 1))
+    return np.clip(np.rint(im), 0, 255).astype(np.uint8)
+
+
+def _in_median_bucket(im):
+    """Survivors whose FP32 value shares the median's upper 16 bits."""
+    o = oracle.edge_view(im)
+    bits = o["M"][o["keep"].astype(bool)].astype(np.float32).view(np.uint32)
+    return int((bits >> 16 == np.float32(o["Mmed"]).view(np.uint32) >> 16).sum())
+
+
+@pytest.mark.parametrize("size,kinds", [((1736, 1150), "n"), ((1736, 1150), "t"), ((1736, 1150), "c"),
+                                        ((1297, 840), "ntsc"), ((640, 480), "ntscntscntscntsc")])
+def test_fp32_guarded_chain(size, kinds):
+    """Views that take the guarded median chain together (more chunks than the
+    short chain's line, fewer than the long one's): striped with noise and plain
+    stripes (more than 128 survivors a chunk in the median's bucket: the refinement
+    launch counts their last digit), textured (fewer: counted one by one) and
+    constant (none). Every form gives the same bits, call after call."""
+    w, h = size
+    rng = np.random.default_rng(17)
+    make = {"n": lambda k: _striped(w, h, rng), "s": lambda k: _striped(w, h),
+            "t": lambda k: synth.image(170 + k, w, h, n_poly=20, texture=True), "c": lambda k: np.full((h, w, 3), 90, np.uint8)}
+    imgs = [make[c](k) for k, c in enumerate(kinds)]
+    chunks = -(-(-(-w // 248) * h) // 16)
+    for im, c in list(zip(imgs, kinds))[:3]:
+        if c != "c":
+            assert (_in_median_bucket(im) > 128 * chunks) == (c != "t"), c
+    vb = synth.pack_views(imgs, in_align=1, out_align=3)
+    b, mb, nb = gpu_edge(vb, "fp32", "unfused")
+    assert [n > 0 for n in nb] == [c != "c" for c in kinds]
+    for form, reps in (("staged", 3), ("plain", 2), ("persistent", 1), ("staged", 1)):
+        a, ma, na = gpu_edge(vb, "fp32", form, reps=reps)
+        assert np.array_equal(a, b) and np.array_equal(ma, mb) and np.array_equal(na, nb), form
+
+
+@pytest.mark.parametrize("precision,chunks", [("fp32", 360), ("fp32", 361), ("fp32", 700), ("fp32", 701),
+                                              ("fp16", 510), ("fp16", 511)])
+@pytest.mark.parametrize("noise", [False, True])
+def test_median_chains_on_either_side_of_their_lines(precision, chunks, noise):
+    """One view of 5 strips with the most chunks that a chain takes and one more,
+    textured and striped with noise, against the unfused form (the long chain)."""
+    w, h = 1240, 16 * chunks // 5
+    assert -(-5 * h // 16) == chunks
+    im = _striped(w, h, np.random.default_rng(19)) if noise else synth.image(180, w, h, n_poly=20, texture=True)
+    vb = synth.pack_views([im], in_align=16, out_align=4)
+    a, ma, na = gpu_edge(vb, precision, "staged", reps=2)
+    b, mb, nb = gpu_edge(vb, precision, "unfused")
+    assert np.array_equal(a, b) and np.array_equal(ma, mb) and np.array_equal(na, nb) and na[0] > 0
