@@ -85,9 +85,13 @@ struct EdgePlan {
   RowChunk* d_rchunks = nullptr;  // the refinement passes' coarser chunks
   RowChunk* d_wide = nullptr;     // FP32: coarser still, for launches over every view (n_wide = 0: not used)
   int n_wide = 0;
-  uint32_t* d_cand = nullptr;     // FP32: median candidates and their counts per view
+  // FP32, each only where some launch of the plan uses it: median candidates of
+  // every view and their counts (the long chain over several views), and the
+  // short chains' counts, of the views that one launch covers
+  uint32_t* d_cand = nullptr;
   uint32_t* d_cand_n = nullptr;
-  uint32_t* d_fine = nullptr;     // FP32: the short chains' counts, of at most kFineViews views
+  uint32_t* d_fine = nullptr;
+  int64_t cand_elems = 0;
   std::vector<int> item_begin, chunk_begin, rchunk_begin;  // per view, size n_views + 1
   void* d_map = nullptr;
   uint32_t* d_hist = nullptr;
@@ -240,6 +244,17 @@ void row_chunks(int v, int W, int H, int slots, std::vector<RowChunk>* out) {
   for (int64_t u0 = 0; u0 < n; u0 += slots) out->push_back(RowChunk{v, (int32_t)u0, (int32_t)std::min(n, u0 + slots), 0});
 }
 
+// Room for the median candidates of the long FP32 chain over several views.
+bool alloc_candidates(EdgePlan* P) {
+  if (hipMalloc(reinterpret_cast<void**>(&P->d_cand), (size_t)P->cand_elems * sizeof(uint32_t)) == hipSuccess &&
+      hipMalloc(reinterpret_cast<void**>(&P->d_cand_n), (size_t)P->n_views * sizeof(uint32_t)) == hipSuccess)
+    return true;
+  (void)hipFree(P->d_cand);  // both or none
+  P->d_cand = nullptr;
+  P->d_cand_n = nullptr;
+  return false;
+}
+
 igsp_status build_edge_plan(const EdgeKey& key, std::shared_ptr<EdgePlan>* out) {
   auto plan = std::make_shared<EdgePlan>();
   plan->key = key;
@@ -305,12 +320,17 @@ igsp_status build_edge_plan(const EdgeKey& key, std::shared_ptr<EdgePlan>* out) 
       upload(&plan->d_wide, wide) != hipSuccess)
     return IGSP_ERR_HIP;
   if (hipMalloc(&plan->d_map, (size_t)std::max<int64_t>(map_elems, 64) * esz) != hipSuccess) return IGSP_ERR_HIP;
-  if (cand_elems > 0 &&
-      (hipMalloc(reinterpret_cast<void**>(&plan->d_cand), (size_t)cand_elems * sizeof(uint32_t)) != hipSuccess ||
-       hipMalloc(reinterpret_cast<void**>(&plan->d_fine),
-                 (size_t)std::min(n, kFineViews) * kFineBins * sizeof(uint32_t)) != hipSuccess ||
-       hipMalloc(reinterpret_cast<void**>(&plan->d_cand_n), (size_t)n * sizeof(uint32_t)) != hipSuccess))
-    return IGSP_ERR_HIP;
+  plan->cand_elems = cand_elems;
+  if (key.precision == IGSP_FP32) {
+    const bool together = median_chain(IGSP_FP32, key.views.data(), n) != kChainLong;
+    bool alone = false;  // (the plain form's launches, one view's counts after another's)
+    for (int v = 0; v < n && !alone; ++v) alone = median_chain(IGSP_FP32, key.views.data() + v, 1) != kChainLong;
+    const int counted = together ? n : (alone ? 1 : 0);
+    if (counted > 0 && hipMalloc(reinterpret_cast<void**>(&plan->d_fine),
+                                 (size_t)counted * kFineBins * sizeof(uint32_t)) != hipSuccess)
+      return IGSP_ERR_HIP;
+    if (n > 1 && !together && !alloc_candidates(plan.get())) return IGSP_ERR_HIP;
+  }
   // refinement histograms of up to two passes, selection states after 0, 1
   // and 2 refinement steps
   const size_t hb = (size_t)n * kBinsMax * sizeof(uint32_t), rb = (size_t)2 * n * kRefineBins * sizeof(uint32_t),
@@ -391,9 +411,11 @@ igsp_status ensure_persistent(EdgePlan* P) {
 }
 
 // Tiles and per-step buffers of the unfused form (gray, blur: int32;
-// magnitude: float; orientation code: byte; all in the plan's map layout).
+// magnitude: float; orientation code: byte; all in the plan's map layout), and
+// the candidates' room that its long chain uses.
 igsp_status ensure_unfused(EdgePlan* P) {
   if (P->uf.items) return IGSP_OK;
+  if (P->key.precision == IGSP_FP32 && P->n_views > 1 && !P->d_cand && !alloc_candidates(P)) return IGSP_ERR_HIP;
   std::vector<UfItem> items;
   for (int v = 0; v < P->n_views; ++v) {
     const igsp_view& d = P->key.views[v];

@@ -401,3 +401,43 @@ def test_median_chains_on_either_side_of_their_lines(precision, chunks, noise):
     a, ma, na = gpu_edge(vb, precision, "staged", reps=2)
     b, mb, nb = gpu_edge(vb, precision, "unfused")
     assert np.array_equal(a, b) and np.array_equal(ma, mb) and np.array_equal(na, nb) and na[0] > 0
+
+
+@pytest.mark.parametrize("sizes", [[(6000, 4000)], [(500, 400)] * 64])
+def test_fp32_plans_hold_what_their_launches_use(sizes):
+    """Beside a map of twice the size, an FP32 plan takes more memory than a BF16
+    one only for what some launch of it uses: one large view neither lists its
+    median's candidates nor counts values; 64 views that take the long chain
+    together list candidates (1/16 of the pixels) and count values for one view at
+    a time, in the plain form, not for all 64 (16 MiB)."""
+    import torch
+
+    import paper_2603_08661_amd as igsp
+
+    dev = torch.device("cuda:0")
+    W, H = (np.array(x, np.int32) for x in zip(*sizes))
+    px = W.astype(np.int64) * H
+    views = (W, H, np.r_[0, np.cumsum(3 * px)[:-1]], np.r_[0, np.cumsum(px)[:-1]])
+    img = torch.randint(0, 256, (int(3 * px.sum()) + 16,), dtype=torch.uint8, device=dev)
+    maps = [torch.zeros(int(px.sum()), device=dev) for _ in range(4)]
+    torch.cuda.synchronize()
+    held = {}
+    for p, out in zip(("fp32", "bf16"), maps):
+        igsp.edge_importance(img, views, out, precision=p, batched="staged")    # kernels loaded
+    for p, out in zip(("fp32", "bf16"), maps):
+        igsp.release_plans()
+        free = torch.cuda.mem_get_info(dev)[0]
+        igsp.edge_importance(img, views, out, precision=p, batched="staged")
+        torch.cuda.synchronize()
+        held[p] = free - torch.cuda.mem_get_info(dev)[0]
+    bf16_map = int((-(-W // 248) * H.astype(np.int64)).sum()) * 512
+    listed = 4 * int(px.sum()) // 16 if len(sizes) > 1 else 0
+    extra = held["fp32"] - held["bf16"] - bf16_map - listed
+    print(f"{extra / 2 ** 20:.1f} MiB besides", flush=True)
+    assert extra < 5 * 2 ** 20
+    # and both forms still give the same bits
+    igsp.edge_importance(img, views, maps[1], precision="fp32", batched="plain")
+    igsp.edge_importance(img, views, maps[2], precision="fp32", batched="unfused")
+    torch.cuda.synchronize()
+    assert torch.equal(maps[0], maps[1]) and torch.equal(maps[0], maps[2])
+    igsp.release_plans()
