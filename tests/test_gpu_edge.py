@@ -203,6 +203,9 @@ def test_more_geometries_than_the_plan_cache_holds():
             compare_view(view_map(E, batches[k], 0), refs[k], "bf16", med[0], nsv[0])
 
 
+# (Views of this size take the short median chain in the plain and staged forms,
+# which lists nothing: here only the unfused form reads the lists. Staged launches
+# do from larger views on: test_fp32_candidate_list_cut_off.)
 @pytest.mark.parametrize("form", ["plain", "staged", "unfused"])
 def test_fp32_median_candidates_overflow_and_fit(form):
     """In launches over several views (staged, unfused), the second FP32
@@ -229,6 +232,8 @@ def test_fp32_median_candidates_overflow_and_fit(form):
     check_batch(vb, "fp32", form)
 
 
+# (The short chain counts every value exactly and has no list: these are stripes
+# with one and with very many values in the median's bucket for it.)
 @pytest.mark.parametrize("form", ["plain", "staged"])
 def test_fp32_candidate_list_without_room(form):
     """The short chain lists the median bucket's values with their counts
@@ -250,6 +255,8 @@ def test_fp32_candidate_list_without_room(form):
     check_batch(synth.pack_views([noisy, flat, noisy], in_align=1, out_align=2), "fp32", form, reps=2)
 
 
+# (688 chunks: FP32's guarded chain on both sides, FP16's long one; the chains'
+# lines are taken by test_median_chains_on_either_side_of_their_lines.)
 @pytest.mark.parametrize("precision", ["fp32", "fp16"])
 @pytest.mark.parametrize("rows", [1376, 1377])
 def test_short_and_long_median_chain(precision, rows):
@@ -441,3 +448,28 @@ def test_fp32_plans_hold_what_their_launches_use(sizes):
     torch.cuda.synchronize()
     assert torch.equal(maps[0], maps[1]) and torch.equal(maps[0], maps[2])
     igsp.release_plans()
+
+
+def test_fp32_candidate_list_cut_off():
+    """Two views of 712 chunks take the long chain together. One is striped with
+    noise: every refinement work-group's list has room for what it finds (2048),
+    but together they find more than the view's list holds (1/16 of its pixels), so
+    the second pass reads the map; the other is textured and fits. Both equal the
+    persistent form, which keeps no lists, bit for bit."""
+    w, h, slots = 1984, 1424, 64
+    rng = np.random.default_rng(23)
+    noisy = np.zeros((h, w, 3)) + ((((np.arange(w) // 4) % 2) * 180) + 30)[None, :, None] + rng.normal(0, 1.0, (h, w, 1))
+    noisy = np.clip(np.rint(noisy), 0, 255).astype(np.uint8)
+    textured = synth.image(190, w, h, n_poly=20, texture=True)
+    assert 8 * h // 16 == 712 and 2 * 8 * h < 40000          # long chain, 64 slots a work-group
+    found = []
+    for im in (noisy, textured):
+        o = oracle.edge_view(im)
+        med = np.float32(o["Mmed"]).view(np.uint32) >> 16
+        hit = o["keep"].astype(bool) & (o["M"].astype(np.float32).view(np.uint32) >> 16 == med)
+        found.append(hit.reshape(8 * h // slots, -1).sum(1))  # a work-group's slots: 8 strips of 8 rows
+    assert found[0].max() <= 2048 and found[0].sum() > w * h // 16 >= found[1].sum(), [f.sum() for f in found]
+    vb = synth.pack_views([noisy, textured], in_align=16, out_align=4)
+    b, mb, nb = gpu_edge(vb, "fp32", "persistent")
+    a, ma, na = gpu_edge(vb, "fp32", "staged", reps=3)
+    assert np.array_equal(a, b) and np.array_equal(ma, mb) and np.array_equal(na, nb) and (na > 0).all()

@@ -110,6 +110,9 @@ def test_workloads(name):
     assert (res["means"][N + w.n_split:] == CANARY).all()
 
 
+# (The one-launch split takes capacities up to 16384 rows, larger ones two launches
+# up to 2048 tiles of 2048 rows, three above: the last two tests of this file lie on
+# either side of both lines.)
 @pytest.mark.parametrize("N,frac,extra", [(0, 0.0, 5), (1, 1.0, 0), (2047, 1.0, 0), (2048, 0.5, 1),
                                           (2049, 0.0, 10), (5000, 0.3, 3), (8193, 0.5, 0), (60000, 0.05, 0),
                                           (64000, 0.024, 0), (64000, 0.024, 1), (70001, 0.01, 0)])

@@ -161,6 +161,8 @@ def test_split_mask_bins(N, keys):
         run(N, N + 3, W, H, c, grad, 0.5, False, N + K, maps, off)
 
 
+# (Three digits are refined now, and bits that a group's keys share passed over:
+# see test_split_mask_refined_to_the_last_bit.)
 @pytest.mark.parametrize("N", [12_000, 70_001])
 @pytest.mark.parametrize("keys", ["equal", "last_bit", "near", "mass_and_near"])
 def test_split_mask_concentrated_scores(N, keys):

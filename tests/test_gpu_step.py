@@ -162,3 +162,56 @@ def test_graph_step_of_the_benchmark_workload():
     assert ref["K"] == K and res["count"] == N + K
     assert (res["means"][N + K:] == 12345.0).all()        # canary rows past N + K
     step.close()
+
+
+@pytest.mark.parametrize("precision,sizes", [("fp32", [(1984, 1424), (1240, 2272), (64, 61)]),
+                                             ("fp16", [(1984, 1424), (300, 200)]),
+                                             ("fp32", [(1297, 840), (1488, 1100), (64, 61)])])
+def test_graph_replays_of_the_other_median_chains(precision, sizes):
+    """The long median chain of FP32 (with its candidate lists) and of FP16, and
+    FP32's guarded chain, recorded in a step (the views of
+    test_graph_replays_match_oracle_and_eager take the short one). Between replays
+    the pixels change (textured, striped with noise), and an eager call of the same
+    geometry uses the same plan. Every replay equals the unfused form's maps bit for
+    bit, and the split repeats."""
+    import torch
+
+    import paper_2603_08661_amd as igsp
+
+    dev = torch.device("cuda:0")
+    rng = np.random.default_rng(29)
+    stripes = lambda w, h: np.clip(np.rint(30 + 180 * ((np.arange(w) // 4) % 2)[None, :, None]  # noqa: E731
+                                           + rng.normal(0, 1.0, (h, w, 1))) + np.zeros(3), 0, 255).astype(np.uint8)
+    scenes = [[synth.image(270 + k, w, h, 20, True) for k, (w, h) in enumerate(sizes)],
+              [stripes(w, h) for w, h in sizes],
+              [stripes(w, h) if k == 0 else synth.image(280 + k, w, h, 20, True) for k, (w, h) in enumerate(sizes)]]
+    packs = [synth.pack_views(s, in_align=16, out_align=4) for s in scenes]
+    vb = packs[0]
+    pixels = [torch.from_numpy(np.concatenate([p.rgb, np.zeros(32, np.uint8)])).to(dev) for p in packs]
+    views = (vb.widths, vb.heights, vb.in_offset, vb.out_offset)
+    img = pixels[0].clone()
+    _, _, _, fresh, mask, cap, host, mk, N = _setup("bf16")
+    g = fresh()
+    pristine = {k: v.clone() for k, v in g.items()}
+    sidx = torch.full((cap,), -1, dtype=torch.int32, device=dev)
+    status = torch.zeros(1, dtype=torch.int32, device=dev)
+    nsplit = torch.full((1,), -1, dtype=torch.int64, device=dev)
+    out, ref, eager = (torch.zeros(vb.out_floats, dtype=torch.float32, device=dev) for _ in range(3))
+    stream = torch.cuda.Stream()
+    step = igsp.Step(img, views, out, g, mask, sidx, status, n_split=nsplit, precision=precision, batched="staged",
+                     stream=stream)
+    for rep in (0, 1, 2, 0):
+        igsp.edge_importance(pixels[rep], views, ref, precision=precision, batched="unfused")
+        igsp.edge_importance(pixels[rep - 1], views, eager, precision=precision, batched="staged")
+        torch.cuda.synchronize()
+        with torch.cuda.stream(stream):
+            img.copy_(pixels[rep])
+            for k in g:
+                g[k].copy_(pristine[k])
+            out.zero_()
+            step.launch(stream)
+        stream.synchronize()
+        assert torch.equal(out, ref) and bool((out > 0).any()), rep
+        assert not torch.equal(out, eager)
+        compare(_las_result(g, sidx, status, nsplit, host, mk), N, cap)
+    step.close()
