@@ -841,37 +841,6 @@ __device__ __forceinline__ SlotAt view_slot(const ViewDesc& vd, int ns, int u, i
   return a;
 }
 
-// The 4 stored values at element e, widened to float32. COHERENT reads them
-// device-coherently (agent-scope relaxed loads, i.e. with the SC1 bit): the
-// persistent form reads values other work-groups of the same launch wrote.
-template <int PREC, bool COHERENT>
-__device__ __forceinline__ void load4(const EdgeLaunch& L, int64_t e, float v[4]) {
-  using S = Store<PREC>;
-  if constexpr (PREC == IGSP_FP32) {
-    uint64_t* p = reinterpret_cast<uint64_t*>(reinterpret_cast<float*>(L.map) + e);
-    uint64_t x, y;
-    if constexpr (COHERENT) {
-      x = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      y = __hip_atomic_load(p + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    } else {
-      const u32x4 q = *as_global(reinterpret_cast<const u32x4*>(p));
-      x = q.x | ((uint64_t)q.y << 32);
-      y = q.z | ((uint64_t)q.w << 32);
-    }
-    v[0] = __uint_as_float((uint32_t)x);
-    v[1] = __uint_as_float((uint32_t)(x >> 32));
-    v[2] = __uint_as_float((uint32_t)y);
-    v[3] = __uint_as_float((uint32_t)(y >> 32));
-  } else {
-    uint64_t* p = reinterpret_cast<uint64_t*>(reinterpret_cast<uint16_t*>(L.map) + e);
-    uint64_t x;
-    if constexpr (COHERENT) x = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    else x = *as_global(p);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) v[i] = S::widen((uint16_t)(x >> (16 * i)));
-  }
-}
-
 // Slots' loads in flight per wavefront in the element-wise walks: 4 in their
 // own launches (lean kernels at eight waves per SIMD), 12 inside the
 // persistent kernel, whose register budget is the stencil's and whose four
@@ -882,8 +851,10 @@ constexpr int kPersistWalkUnroll = 12;
 
 constexpr int kLdsCand = 2048;  // candidates a work-group gathers before it flushes them
 
-// The 4 stored values of a lane as raw words (FP32: one each; FP16, BF16: two
-// values a word).
+// The 4 stored values of a lane at element e as raw words (FP32: one each;
+// FP16, BF16: two values a word). COHERENT reads them device-coherently
+// (agent-scope relaxed loads, i.e. with the SC1 bit): the persistent form reads
+// values other work-groups of the same launch wrote.
 template <int PREC> struct Raw4 {
   static constexpr int kWords = PREC == IGSP_FP32 ? 4 : 2;
   uint32_t w[kWords];
@@ -908,6 +879,17 @@ __device__ __forceinline__ Raw4<PREC> load_raw4(const EdgeLaunch& L, int64_t e) 
 #pragma unroll
   for (int i = 0; i < Raw4<PREC>::kWords; ++i) r.w[i] = (uint32_t)(x[i >> 1] >> (32 * (i & 1)));
   return r;
+}
+
+// The same widened to float32.
+template <int PREC, bool COHERENT>
+__device__ __forceinline__ void load4(const EdgeLaunch& L, int64_t e, float v[4]) {
+  const Raw4<PREC> r = load_raw4<PREC, COHERENT>(L, e);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    if constexpr (PREC == IGSP_FP32) v[i] = __uint_as_float(r.w[i]);
+    else v[i] = Store<PREC>::widen((uint16_t)(r.w[i >> 1] >> (16 * (i & 1))));
+  }
 }
 
 // Which of a lane's 4 values lie in the resolved bucket (bit i: value i), and
