@@ -259,7 +259,8 @@ def kernel_source_digest() -> str:
     import hashlib
 
     h = hashlib.sha256()
-    for name in ("edge_kernels.hip", "select_kernels.hip", "las_kernels.hip", "igsp_api.hip", "igsp_internal.h"):
+    for name in ("edge_kernels.hip", "select_kernels.hip", "las_kernels.hip", "igsp_api.hip", "igsp_internal.h",
+                 "schedule.h"):
         h.update(open(os.path.join(ROOT, "paper_2603_08661_amd", "csrc", name), "rb").read())
     return h.hexdigest()
 

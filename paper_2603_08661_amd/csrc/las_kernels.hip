@@ -469,8 +469,8 @@ __global__ __launch_bounds__(kLasThreads) __attribute__((amdgpu_waves_per_eu(4))
 // A small plain split (capacity <= kLasSmallCapacity rows) in one launch by
 // one work-group: it counts the selected rows, takes the capacity decision,
 // then compacts and splits them round by round (8 rows per thread and
-// round). Same rows, same order, same all-or-nothing rule as the three
-// launches; a call then costs one launch instead of two. The line lies where
+// round). Same rows, same order, same all-or-nothing rule as the larger
+// splits' launches; a call then costs one launch instead of two. The line lies where
 // one work-group's time reaches the other launch's: a call of 10k rows at
 // 10 / 30% takes 12.2 / 14.3 us (16.5 with two launches), 14k 12.2 / 16.6,
 // 20k 16.2 / 22.1, 50k 33.0 / 48.2 (16.5 / 16.7).
