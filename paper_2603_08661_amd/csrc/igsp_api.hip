@@ -93,6 +93,8 @@ struct EdgePlan {
   uint32_t* d_fine = nullptr;
   int64_t cand_elems = 0;
   std::vector<int> item_begin, chunk_begin, rchunk_begin;  // per view, size n_views + 1
+  int chain_all = kChainLong;      // median chain of a launch over every view
+  std::vector<int> chain_one;      // and of one over a single view
   void* d_map = nullptr;
   uint32_t* d_hist = nullptr;
   uint32_t* d_rhist = nullptr;
@@ -321,11 +323,12 @@ igsp_status build_edge_plan(const EdgeKey& key, std::shared_ptr<EdgePlan>* out) 
     return IGSP_ERR_HIP;
   if (hipMalloc(&plan->d_map, (size_t)std::max<int64_t>(map_elems, 64) * esz) != hipSuccess) return IGSP_ERR_HIP;
   plan->cand_elems = cand_elems;
+  plan->chain_all = median_chain(key.precision, key.views.data(), n);
+  for (const igsp_view& d : key.views) plan->chain_one.push_back(median_chain(key.precision, &d, 1));
   if (key.precision == IGSP_FP32) {
-    const bool together = median_chain(IGSP_FP32, key.views.data(), n) != kChainLong;
-    bool alone = false;  // (the plain form's launches, one view's counts after another's)
-    for (int v = 0; v < n && !alone; ++v) alone = median_chain(IGSP_FP32, key.views.data() + v, 1) != kChainLong;
-    const int counted = together ? n : (alone ? 1 : 0);
+    const bool together = plan->chain_all != kChainLong;
+    const bool alone = std::any_of(plan->chain_one.begin(), plan->chain_one.end(), [](int c) { return c != kChainLong; });
+    const int counted = together ? n : (alone ? 1 : 0);  // (the plain form counts one view after another)
     if (counted > 0 && hipMalloc(reinterpret_cast<void**>(&plan->d_fine),
                                  (size_t)counted * kFineBins * sizeof(uint32_t)) != hipSuccess)
       return IGSP_ERR_HIP;
@@ -525,7 +528,7 @@ igsp_status enqueue_edge(EdgePlan* P, const uint8_t* images, int64_t img_end, fl
   hipEvent_t* ev = L.stage_events;
   auto mark = [&](int k, hipStream_t st) -> hipError_t { return ev ? hipEventRecord(ev[k], st) : hipSuccess; };
   auto chain = [&](int v0, int v1) {
-    return form == IGSP_UNFUSED ? (int)kChainLong : median_chain(L.precision, P->key.views.data() + v0, v1 - v0);
+    return form == IGSP_UNFUSED ? (int)kChainLong : (v0 == 0 && v1 == n ? P->chain_all : P->chain_one[v0]);
   };
   // median selection (+ refinement passes) of views [v0, v1); the last
   // selection step is taken by the normalisation
